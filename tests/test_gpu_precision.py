@@ -1,0 +1,51 @@
+"""How far attention is from 64-bit arithmetic, in the root mean square of the result: what the data types give and no less.
+
+Bound for fp32, in units u = 2^-24 (a rounding is u / sqrt(3) in the mean): a score of head_dim D in chains of L products that
+meet pairwise is off by sqrt(L / 2 + log2(D / L)) roundings, 1.6 u at most (D = 128, L = 8), and its weight by as much; the
+weight itself by half a u; a tile's share of the output (chains of up to 8 keys, pairwise) and up to 20 tiles added one by one
+by sqrt(4 + 2 + 20 / 2) roundings, 2.3 u; key ranges, sums and quotient by another u.  Together 3.0 u; the bound is 3.6."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2510_09608_amd as sv
+import sv_inputs as si
+from oracle import sv_oracle as orc
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+U = 2.0 ** -24
+
+
+def cache_of(dtype, hq, hkv, d, lens, max_q, seed):
+    """A cache whose stream b holds lens[b] tokens, every one the beginning of the same rows; and those rows."""
+    w = si.Workload("p", 1, hq, hkv, d, dtype, 2, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, seed)
+    cache = sv.Cache(1, hq, hkv, d, sv.SV_DTYPE_F32 if dtype == "f32" else sv.SV_DTYPE_BF16, sv.SV_ROPE_NONE, 1e4, (0, 0, 0),
+                     len(lens), max(lens) + 8, max_q)
+    _, k, v = w.qkv(0, np.arange(max(lens)))
+    for b, n in enumerate(lens):
+        cache.append(b, 0, np.zeros(n, np.uint8), None, gu.dev(k[:n], w), gu.dev(v[:n], w))
+    return cache, w, k.astype(np.float64), v.astype(np.float64)
+
+
+def rms_error(o, ref):
+    return float(np.sqrt(np.mean((gu.host(o) - ref) ** 2) / np.mean(ref ** 2)))
+
+
+def chunk_error(dtype, hq, hkv, d, n_kv, n_q, causal):
+    print(f"chunk {dtype} {hq}/{hkv} x {d}: {n_q} queries, {n_kv} keys", flush=True)
+    cache, w, k, v = cache_of(dtype, hq, hkv, d, [n_kv], n_q, 9000 + n_kv)
+    q = w.qkv(0, np.arange(60000, 60000 + n_q))[0]
+    qd = gu.dev(q, w)
+    o = torch.empty_like(qd)
+    cache.attn_chunk(0, 0, qd, o, causal)
+    return rms_error(o, orc.gqa_attention(q.astype(np.float64), k, v, np.arange(n_kv - n_q, n_kv), causal))
+
+
+@pytest.mark.parametrize("hq,hkv,d,n_kv,n_q,causal", [
+    (28, 4, 128, 400, 64, True), (8, 2, 128, 72, 16, True), (8, 2, 128, 2600, 300, True), (28, 4, 128, 1500, 9, False),
+    (2, 1, 64, 400, 16, True), (8, 8, 64, 400, 130, True), (8, 8, 64, 2600, 500, True)])
+def test_fp32_chunk_is_as_exact_as_its_sums(hq, hkv, d, n_kv, n_q, causal):
+    """Chunk prefill of both fp32 kernels and their merge."""
+    assert chunk_error("f32", hq, hkv, d, n_kv, n_q, causal) <= 3.6 * U
