@@ -49,3 +49,23 @@ def chunk_error(dtype, hq, hkv, d, n_kv, n_q, causal):
 def test_fp32_chunk_is_as_exact_as_its_sums(hq, hkv, d, n_kv, n_q, causal):
     """Chunk prefill of both fp32 kernels and their merge."""
     assert chunk_error("f32", hq, hkv, d, n_kv, n_q, causal) <= 3.6 * U
+
+
+def decode_error(dtype, hq, hkv, d, lens, steps=12):
+    print(f"decode {dtype} {hq}/{hkv} x {d}: {lens} keys", flush=True)
+    cache, w, k, v = cache_of(dtype, hq, hkv, d, lens, 16, 9100 + sum(lens))
+    q = w.qkv(0, np.arange(60000, 60000 + steps * len(lens)))[0].reshape(steps, len(lens), hq, d)
+    o = torch.stack([gu.dev(x, w) for x in q])
+    for i in range(steps):
+        cache.attn_decode(0, list(range(len(lens))), gu.dev(q[i], w), o[i])
+    at = np.tile(np.array(lens) - 1, steps)
+    ref = orc.gqa_attention(q.reshape(-1, hq, d).astype(np.float64), k, v, at, True)
+    return rms_error(o, ref.reshape(q.shape))
+
+
+@pytest.mark.parametrize("hq,hkv,d,lens", [
+    (8, 2, 128, [400]), (28, 4, 128, [72]), (28, 4, 128, [3000]), (2, 1, 64, [72]), (8, 8, 64, [1500]),
+    (8, 2, 128, [400, 311, 1700]), (8, 8, 64, [300, 20, 900, 1500, 64])])
+def test_fp32_decode_is_as_exact_as_its_sums(hq, hkv, d, lens):
+    """Decode of one stream (key ranges merged in the launch) and of several (merged by a launch of its own)."""
+    assert decode_error("f32", hq, hkv, d, lens) <= 3.6 * U
