@@ -33,14 +33,16 @@ def rms_error(o, ref):
     return float(np.sqrt(np.mean((gu.host(o) - ref) ** 2) / np.mean(ref ** 2)))
 
 
-def chunk_error(dtype, hq, hkv, d, n_kv, n_q, causal):
-    print(f"chunk {dtype} {hq}/{hkv} x {d}: {n_q} queries, {n_kv} keys", flush=True)
+def chunk_error(dtype, hq, hkv, d, n_kv, n_q, causal, splits=0):
+    print(f"chunk {dtype} {hq}/{hkv} x {d}: {n_q} queries, {n_kv} keys, {splits} ranges", flush=True)
     cache, w, k, v = cache_of(dtype, hq, hkv, d, [n_kv], n_q, 9000 + n_kv)
+    cache.set_option(sv.SV_OPT_CHUNK_SPLITS, splits)
     q = w.qkv(0, np.arange(60000, 60000 + n_q))[0]
     qd = gu.dev(q, w)
     o = torch.empty_like(qd)
     cache.attn_chunk(0, 0, qd, o, causal)
-    return rms_error(o, orc.gqa_attention(q.astype(np.float64), k, v, np.arange(n_kv - n_q, n_kv), causal))
+    ref = orc.gqa_attention(q.astype(np.float64), k, v, np.arange(n_kv - n_q, n_kv), causal)
+    return rms_error(o, ref), ref
 
 
 @pytest.mark.parametrize("hq,hkv,d,n_kv,n_q,causal", [
@@ -48,7 +50,7 @@ def chunk_error(dtype, hq, hkv, d, n_kv, n_q, causal):
     (2, 1, 64, 400, 16, True), (8, 8, 64, 400, 130, True), (8, 8, 64, 2600, 500, True)])
 def test_fp32_chunk_is_as_exact_as_its_sums(hq, hkv, d, n_kv, n_q, causal):
     """Chunk prefill of both fp32 kernels and their merge."""
-    assert chunk_error("f32", hq, hkv, d, n_kv, n_q, causal) <= 3.6 * U
+    assert chunk_error("f32", hq, hkv, d, n_kv, n_q, causal)[0] <= 3.6 * U
 
 
 def decode_error(dtype, hq, hkv, d, lens, steps=12):
@@ -82,4 +84,12 @@ def test_bf16_decode_of_head_dim_64_rounds_its_result_alone(hq, hkv, lens):
     """Probabilities keep their 24 bits: what is left is the result's rounding.  (fp32 sums of some thousand products are off
     by about 1e-6, in quadrature with 1.7e-3; with probabilities rounded to bf16 it would be 1.2 times as much.)"""
     err, ref = decode_error("bf16", hq, hkv, 64, lens)
+    assert err <= 1.002 * rounded_to_bf16(ref)
+
+
+@pytest.mark.parametrize("hq,hkv,n_kv,n_q,causal,splits", [
+    (16, 2, 400, 64, True, 1), (14, 2, 1500, 130, False, 1), (4, 4, 33, 33, True, 1), (16, 2, 700, 700, True, 1)])
+def test_bf16_chunk_of_head_dim_64_rounds_its_result_alone(hq, hkv, n_kv, n_q, causal, splits):
+    """Probabilities to 16 bits and more (2^-17 in quadrature with 2^-9.2), sums and partial results in fp32."""
+    err, ref = chunk_error("bf16", hq, hkv, 64, n_kv, n_q, causal, splits)
     assert err <= 1.002 * rounded_to_bf16(ref)
