@@ -88,7 +88,8 @@ def test_bf16_decode_of_head_dim_64_rounds_its_result_alone(hq, hkv, lens):
 
 
 @pytest.mark.parametrize("hq,hkv,n_kv,n_q,causal,splits", [
-    (16, 2, 400, 64, True, 1), (14, 2, 1500, 130, False, 1), (4, 4, 33, 33, True, 1), (16, 2, 700, 700, True, 1)])
+    (16, 2, 400, 64, True, 1), (14, 2, 1500, 130, False, 1), (4, 4, 33, 33, True, 1), (16, 2, 700, 700, True, 1),
+    (16, 2, 5392, 256, True, 0), (4, 4, 1500, 300, True, 0), (14, 2, 900, 20, False, 9)])
 def test_bf16_chunk_of_head_dim_64_rounds_its_result_alone(hq, hkv, n_kv, n_q, causal, splits):
     """Probabilities to 16 bits and more (2^-17 in quadrature with 2^-9.2), sums and partial results in fp32."""
     err, ref = chunk_error("bf16", hq, hkv, 64, n_kv, n_q, causal, splits)
