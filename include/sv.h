@@ -105,7 +105,10 @@ SV_API int sv_cache_destroy(sv_cache* c);
  * sv_cache_set_option -- per-handle launch overrides; implements no passage of the paper.  Every option
  * defaults to 0 = "let the library choose" (what all measurements use); a positive value forces
  *   SV_OPT_CHUNK_SPLITS           the number of key ranges of sv_attn_chunk's matrix-core kernel,
- *   SV_OPT_DECODE_TILES_PER_WAVE  the 32-key tiles each wavefront of the decode kernel takes (1..16),
+ *   SV_OPT_DECODE_TILES_PER_WAVE  the 32-key tiles each wavefront of the decode kernel takes (1..16);
+ *                                 with SV_MERGE_ONE_LOOK added (a test seam, results unchanged) a workgroup of the
+ *                                 decode kernels that does not find the other key ranges' results at its first look
+ *                                 leaves its share of the merge to those that are late, instead of after 4096 looks,
  *   SV_OPT_DECODE_SPLITS          the number of key ranges of the generic row kernel,
  *   SV_OPT_CHUNK_STORE            who stores a chunk's K/V in sv_stream_step on a matrix-core cache: 1 = always a
  *                                 launch of its own, 2 = the attention launch whenever it can (chunks of at most
@@ -118,7 +121,8 @@ enum {
   SV_OPT_DECODE_TILES_PER_WAVE = 1,
   SV_OPT_DECODE_SPLITS = 2,
   SV_OPT_CHUNK_STORE = 3,
-  SV_OPT_COUNT_ = 4
+  SV_OPT_COUNT_ = 4,
+  SV_MERGE_ONE_LOOK = 1 << 16
 };
 SV_API int sv_cache_set_option(sv_cache* c, int option, int value);
 
@@ -201,6 +205,8 @@ SV_API int sv_attn_chunk(sv_cache* c, int stream_id, int layer, const void* q_de
  * (text decoding against the compact cache, Sec. 2.1 / Sec. 3.3).  Streams may
  * have different lengths (split-KV, variable length).  q_dev and o_dev are
  * [n_list][n_q_heads][head_dim], row b belongs to stream_ids_host[b].
+ * The workgroups of this and of the other decode launches exchange results inside the launch, but no result depends on
+ * when they run: where other work holds part of the GPU it comes later and is the same.
  */
 SV_API int sv_attn_decode(sv_cache* c, int layer, const int32_t* stream_ids_host, int n_list,
                    const void* q_dev, void* o_dev, void* hip_stream);
@@ -216,7 +222,8 @@ SV_API int sv_attn_decode(sv_cache* c, int layer, const int32_t* stream_ids_host
  * cut into fewer, longer key ranges.  Every call on one GPU shares the array: calls that overlap in time on
  * one GPU (different streams, different handles) race; calls ordered on one stream do not.  The array is
  * zero when the library is loaded and needs no clearing between calls: the partial results in it are 64-bit words
- * {value, launch tag}, which the call's own workgroups read until they carry the tag of this launch; the tags are kept in
+ * {value, launch tag}, which the call's own workgroups read until they carry the tag of this launch (or, where some are made
+ * late by other work, leave to those); the tags are kept in
  * the array itself and moved on by every launch.
  * Nothing in a launch depends on host state that changes from call to call, so a captured call may be replayed
  * while the cache is unchanged.

@@ -264,3 +264,52 @@ def test_fp32_chunk_of_few_rows(hq, hkv, d, n_kv, n_q, causal, splits):
     """fp32 chunk prefill with up to 64 rows per kv head (the wavefronts share them and deal out the tiles) and just above:
     one to all wavefronts with a tile, rows that see nothing of a range, ragged last rows and tiles."""
     attn_case("f32", hq, hkv, d, n_kv, n_q, causal, 7000 + n_kv, splits)
+
+
+# ---- merges inside a decode launch that do not wait for each other ---------------------------------------------------
+
+@pytest.mark.parametrize("dtype,hq,hkv,d,lens", [
+    ("bf16", 28, 4, 128, [5392]), ("bf16", 28, 4, 128, [300]), ("bf16", 16, 2, 64, [5392]), ("bf16", 64, 64, 128, [300]),
+    ("bf16", 3, 1, 128, [20000]), ("f32", 8, 2, 128, [5392]), ("f32", 2, 1, 64, [130]), ("bf16", 8, 8, 64, [9000]),
+    ("bf16", 28, 4, 128, [9000, 300, 4097, 128, 5000, 1, 2500]), ("bf16", 7, 1, 128, [150 + 37 * i for i in range(40)]),
+    ("bf16", 3, 1, 128, [20000, 20000]), ("bf16", 14, 2, 64, [2300, 5000, 64])])
+def test_decode_merge_left_to_late_workgroups(dtype, hq, hkv, d, lens):
+    """Workgroups that look for the others' results once and then leave their share of the merge to whoever publishes later:
+    bit for bit the result of those that wait, launch after launch (a header that ran ahead, or words taken for those of the
+    launch before, would show in the next), on shorter rows in between, and beside another stream's work."""
+    w = si.Workload("l", 1, hq, hkv, d, dtype, 2, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, 9400 + len(lens))
+    n_s = len(lens)
+    cache = sv.Cache(1, hq, hkv, d, sv.SV_DTYPE_F32 if dtype == "f32" else sv.SV_DTYPE_BF16, sv.SV_ROPE_NONE, 1e4, (0, 0, 0),
+                     n_s + 1, max(lens) + 8, 16)
+    _, k, v = w.qkv(0, np.arange(max(lens)))
+    for b, n in enumerate(lens + [max(1, min(lens) // 2)]):
+        cache.append(b, 0, np.zeros(n, np.uint8), None, gu.dev(k[:n], w), gu.dev(v[:n], w))
+    ids, short = list(range(n_s)), [n_s]
+    q = [gu.dev(x, w) for x in w.qkv(0, np.arange(60000, 60000 + 6 * (n_s + 1)))[0].reshape(6, n_s + 1, hq, d)]
+
+    def launches(fn, looks, beside):
+        cache.set_option(sv.SV_OPT_DECODE_TILES_PER_WAVE, looks)
+        out = []
+        for i in range(24):
+            if beside and i % 4 == 0:
+                other.wait_stream(torch.cuda.current_stream())
+                with torch.cuda.stream(other):
+                    a @ a
+            x = q[i % 6]
+            o = torch.full_like(x, float("nan"))
+            fn(0, ids, x[:n_s], o[:n_s])
+            if i % 3 == 0:
+                fn(0, short, x[n_s:], o[n_s:])
+            out.append(o)
+        torch.cuda.synchronize()
+        return out
+    other, a = torch.cuda.Stream(), torch.randn(2048, 2048, device="cuda:0")
+    fns = [cache.attn_decode] + ([cache.attn_decode_static] if dtype == "bf16" else [])
+    for fn in fns:
+        print(f"{dtype} {hq}/{hkv} x {d} {lens[:3]} {fn.__name__}", flush=True)
+        want = launches(fn, 0, False)
+        assert not torch.isnan(want[1][:n_s]).any()
+        for beside in (False, True, False):
+            got = launches(fn, sv.SV_MERGE_ONE_LOOK, beside)
+            for i, (x, y) in enumerate(zip(got, want)):
+                assert torch.equal(x[:n_s], y[:n_s]) and (i % 3 or torch.equal(x[n_s:], y[n_s:])), (fn.__name__, beside, i)
