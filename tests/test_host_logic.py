@@ -173,3 +173,16 @@ def test_options_and_flags():
     assert lib.sv_cache_bytes(C.byref(cfg)) == 0
     cfg.flags, cfg.capacity_tokens = 0, (1 << 24) + 1            # slots are indexed with 32-bit arithmetic
     assert lib.sv_cache_bytes(C.byref(cfg)) == 0
+
+
+def test_arena_holds_decode_batches_of_the_rows_that_occur():
+    """A bf16 cache of one stream and one layer never decodes a batch of its own; with many wide heads the room for 64 rows
+    would be 140 MB of its arena."""
+    hq, hkv, cap = 2040, 255, 64
+    cfg = B.SvConfig(n_layers=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, dtype=B.SV_DTYPE_BF16, rope_mode=B.SV_ROPE_NONE,
+                     rope_theta=1e4, mrope_sections=(C.c_int32 * 3)(0, 0, 0), n_streams=1, capacity_tokens=cap, max_q_tokens=16,
+                     flags=0)
+    kv = 2 * 2 * hkv * cap * 128 * 2
+    split_kv = 4096 * hq * (128 * 4 + 16) + 4096 * hkv * 4          # chunk prefill: partial rows, (max, sum, scale), counters
+    single = 128 * hq * 132 * 8                                     # one stream's key ranges
+    assert kv + split_kv + single < B.lib().sv_cache_bytes(C.byref(cfg)) < kv + split_kv + single + (1 << 20)
