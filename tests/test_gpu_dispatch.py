@@ -313,3 +313,167 @@ def test_decode_merge_left_to_late_workgroups(dtype, hq, hkv, d, lens):
             got = launches(fn, sv.SV_MERGE_ONE_LOOK, beside)
             for i, (x, y) in enumerate(zip(got, want)):
                 assert torch.equal(x[:n_s], y[:n_s]) and (i % 3 or torch.equal(x[n_s:], y[n_s:])), (fn.__name__, beside, i)
+
+
+@pytest.mark.parametrize("hq,hkv,d,n_s,layers", [(28, 4, 128, 1, 1), (16, 2, 64, 2, 1), (8, 8, 128, 1, 3)])
+def test_decode_lists_longer_than_the_arena_has_rows_for(hq, hkv, d, n_s, layers):
+    """Lists that name a stream more than once, longer than the number of streams and of layers: several launches."""
+    lens = [900, 333][:n_s]
+    w = si.Workload("a", 1, hq, hkv, d, "bf16", 2, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, 9600)
+    cache = sv.Cache(layers, hq, hkv, d, sv.SV_DTYPE_BF16, sv.SV_ROPE_NONE, 1e4, (0, 0, 0), n_s, 1000, 16)
+    _, k, v = w.qkv(0, np.arange(900))
+    for b, n in enumerate(lens):
+        for layer in range(layers):
+            cache.append(b, layer, np.zeros(n, np.uint8) if layer == 0 else None, None, gu.dev(k[:n], w), gu.dev(v[:n], w))
+    ids = [(3 * i) % n_s for i in range(7)]
+    q = w.qkv(0, np.arange(60000, 60007))[0]
+    o = torch.full((7, hq, d), float("nan"), device="cuda:0", dtype=torch.bfloat16)
+    print(f"{hq}/{hkv} x {d}: {ids} of {n_s} streams, {layers} layers", flush=True)
+    cache.attn_decode(0, ids, gu.dev(q, w), o)
+    want = batch_ref(q, [(k, v)] * 7, [lens[i] for i in ids], hq // hkv)
+    assert gu.max_err(gu.host(o), want) <= gu.TOL["bf16"]
+
+
+# ---- values of kernels that other tests reach by shape only -----------------------------------------------------------
+
+@pytest.mark.parametrize("hq,hkv,d,lens", [
+    (8, 2, 128, [1, 15, 16, 17, 64, 65, 500]), (2, 1, 64, [700, 3]), (21, 3, 128, [1500, 129, 128]),
+    (7, 1, 64, [40 + 13 * i for i in range(70)]),                      # more rows than one launch takes
+    (8, 8, 128, [7000, 6000])])                                         # 106 MB of K and V: non-temporal loads
+def test_fp32_decode_batch_values(hq, hkv, d, lens):
+    """Several fp32 rows in a launch: sv_attn_decode, then a fused sv_decode_step with the K and V it stores (rows of one
+    tile, of one key range, of many, and their merge)."""
+    w = si.Workload("f", 1, hq, hkv, d, "f32", 0, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, 9700 + len(lens))
+    n_s = len(lens)
+    cache = sv.Cache(1, hq, hkv, d, sv.SV_DTYPE_F32, sv.SV_ROPE_1D, 1e4, (0, 0, 0), n_s, max(lens) + 2, 16)
+    base, kv = w.qkv(0, np.arange(max(lens))), []
+    for b, n in enumerate(lens):
+        k, v = np.roll(base[1], 13 * b, axis=0)[:n], np.roll(base[2], 29 * b, axis=0)[:n]
+        kv.append((orc.rope(k, np.repeat(np.arange(n)[:, None], 3, 1), 0, 1e4, (0, 0, 0)), v))
+        cache.append(b, 0, np.zeros(n, np.uint8), None, gu.dev(k, w), gu.dev(v, w))
+    q = w.qkv(0, np.arange(50000, 50000 + n_s))[0]
+    print(f"fp32 decode batch {hq}/{hkv} x {d} rows {n_s}", flush=True)
+    ids = list(range(n_s))
+    od = torch.full((n_s, hq, d), float("nan"), device="cuda:0")
+    cache.attn_decode(0, ids, gu.dev(q, w), od)
+    assert gu.max_err(gu.host(od), batch_ref(q, kv, lens, hq // hkv)) <= gu.TOL["f32"]
+    qn, kn, vn = w.qkv(0, np.arange(60000, 60000 + n_s))
+    od = torch.full((n_s, hq, d), float("nan"), device="cuda:0")
+    cache.decode_step(0, ids, gu.dev(qn, w), gu.dev(kn, w), gu.dev(vn, w), od)
+    kv2, qr = [], []
+    for b, n in enumerate(lens):
+        pos = np.full((1, 3), n)
+        kr = orc.rope(kn[b:b + 1], pos, 0, 1e4, (0, 0, 0))
+        kv2.append((np.concatenate([kv[b][0], kr]), np.concatenate([kv[b][1], vn[b:b + 1]])))
+        qr.append(orc.rope(qn[b:b + 1], pos, 0, 1e4, (0, 0, 0))[0])
+        assert gu.max_err(cache.read_kv(b, 0, 0, n, 1), kr) <= 1e-5 and np.array_equal(cache.read_kv(b, 0, 1, n, 1), vn[b:b + 1])
+    assert gu.max_err(gu.host(od), batch_ref(np.stack(qr), kv2, [n + 1 for n in lens], hq // hkv)) <= gu.TOL["f32"]
+
+
+def test_fp32_decode_of_one_long_stream():
+    """12400 keys of 8 kv heads of 128, 102 MB: the single-stream kernel with non-temporal loads."""
+    cache, w, q, k, v = attn_case("f32", 8, 8, 128, 12400, 1, True, 9800)
+    qd = gu.dev(q, w)
+    od = torch.empty_like(qd)
+    cache.attn_decode(0, [0], qd, od)
+    ref = orc.gqa_attention(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), np.array([12399]), True)
+    assert gu.max_err(gu.host(od), ref) <= gu.TOL["f32"]
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d", [("bf16", 16, 2, 64), ("f32", 8, 2, 128), ("f32", 8, 8, 64), ("f32", 2, 1, 64)])
+@pytest.mark.parametrize("n_q", [200, 5])
+def test_wide_score_range_of_every_matrix_core_layout(dtype, hq, hkv, d, n_q):
+    """Row maxima that jump by tens to hundreds of binary orders between key tiles, as in test_attn_chunk_wide_score_range:
+    chunk prefill (with 5 queries in fp32 the kernel for few rows) and decode of one and of two rows.
+
+    fp32: a score s is off by up to 4 x 1.6 times 2^-24 of its size (see test_gpu_precision) and its weight by as much of
+    itself.  What that does to a row's output: the largest weight p multiplies a value within (1 - p) x 9 of the output (values
+    are up to 4.5), the others, 1 - p together, values within 9 of it."""
+    n_kv = 1100
+    w = si.Workload("a", 1, hq, hkv, d, dtype, 2, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, 9900)
+    q, k, v = w.qkv(0, np.arange(n_kv))
+    q, k = q[n_kv - n_q:], k.copy()
+    k[0:64] *= 1.0 / 64
+    k[192:256] *= 16
+    k[640:704] *= 32
+    k[901] *= 128
+    k[n_kv - 100:n_kv - 90] *= 8
+    q64, k64, v64 = (x.astype(np.float64) for x in (q, k, v))
+    scores = np.einsum("qhd,khd->qhk", q64, np.repeat(k64, hq // hkv, 1)) / np.sqrt(d)
+
+    def check(o, at, causal):
+        """o: the outputs of the last len(at) queries, at: their slots"""
+        ref = orc.gqa_attention(q64[-len(at):], k64, v64, at, causal)
+        if dtype == "bf16":
+            assert gu.max_err(gu.host(o), ref) <= gu.TOL["bf16"]
+            return
+        s = scores[-len(at):]
+        if causal:
+            s = np.where(np.arange(n_kv) <= at[:, None, None], s, -np.inf)
+        p = np.exp(s - s.max(-1, keepdims=True))
+        rest = 1 - 1 / p.sum(-1)
+        size = np.abs(np.where(np.isfinite(s), s, 0)).max(-1)
+        tol = gu.TOL["f32"] + 4 * 1.6 * 2.0 ** -24 * size * rest * 18
+        gu.max_err(gu.host(o), ref)
+        assert (np.abs(gu.host(o) - ref).max(-1) <= tol).all()
+    cache = sv.Cache(1, hq, hkv, d, sv.SV_DTYPE_F32 if dtype == "f32" else sv.SV_DTYPE_BF16, sv.SV_ROPE_NONE, 1e4, (0, 0, 0), 2,
+                     n_kv + 8, n_q)
+    for s in range(2):
+        cache.append(s, 0, np.zeros(n_kv, np.uint8), None, gu.dev(k, w), gu.dev(v, w))
+    qd = gu.dev(q, w)
+    for causal in (True, False):
+        for splits in (0, 1, 4):
+            print(f"wide scores {dtype} {hq}/{hkv} x {d} n_q={n_q} causal={causal} splits={splits}", flush=True)
+            cache.set_option(sv.SV_OPT_CHUNK_SPLITS, splits)
+            od = torch.full_like(qd, float("nan"))
+            cache.attn_chunk(0, 0, qd, od, causal)
+            check(od, np.arange(n_kv - n_q, n_kv), causal)
+    for ids in ([0], [0, 1]):
+        x = qd[-len(ids):].contiguous()
+        od = torch.full_like(x, float("nan"))
+        cache.attn_decode(0, ids, x, od)
+        check(od, np.full(len(ids), n_kv - 1), True)
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d", [("f32", 2, 2, 64), ("f32", 4, 2, 128), ("f32", 16, 4, 64), ("f32", 7, 1, 128),
+                                           ("f32", 16, 2, 128), ("bf16", 3, 3, 64), ("bf16", 8, 2, 64), ("bf16", 14, 2, 64),
+                                           ("bf16", 16, 2, 64), ("bf16", 4, 2, 64)])
+def test_generic_row_kernels_of_every_layout(dtype, hq, hkv, d):
+    """SV_FLAG_GENERIC_KERNELS on the types and sizes that the matrix-core kernels normally take: chunk prefill, decode of one
+    and of three rows, a fused decode step, one and several key ranges."""
+    tol, rope = gu.TOL[dtype], (sv.SV_ROPE_1D, 1e4, (0, 0, 0))
+    w = si.Workload("g", 1, hq, hkv, d, dtype, 0, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, 9950 + hq)
+    lens, n_q = [333, 70, 1], 41
+    base = w.qkv(0, np.arange(max(lens)))
+    for splits in (0, 1, 5):
+        print(f"generic {dtype} {hq}/{hkv} x {d} splits={splits}", flush=True)
+        cache = sv.Cache(1, hq, hkv, d, sv.SV_DTYPE_F32 if dtype == "f32" else sv.SV_DTYPE_BF16, *rope, 3, max(lens) + 8, n_q,
+                         flags=sv.SV_FLAG_GENERIC_KERNELS)
+        cache.set_option(sv.SV_OPT_DECODE_SPLITS, splits)
+        kv = []
+        for b, n in enumerate(lens):
+            k, v = base[1][:n], base[2][:n]
+            cache.append(b, 0, np.zeros(n, np.uint8), None, gu.dev(k, w), gu.dev(v, w))
+            kv.append((cache.read_kv(b, 0, 0, 0, n).astype(np.float64), v))
+        q = base[0][:n_q]
+        qd = gu.dev(q, w)
+        od = torch.full_like(qd, float("nan"))
+        cache.attn_chunk(0, 0, qd, od, True)
+        ref = orc.gqa_attention(q.astype(np.float64), kv[0][0], kv[0][1].astype(np.float64), np.arange(333 - n_q, 333), True)
+        assert gu.max_err(gu.host(od), ref) <= tol
+        for ids in ([0], [2, 0, 1]):
+            x = qd[:len(ids)].contiguous()
+            od = torch.full_like(x, float("nan"))
+            cache.attn_decode(0, ids, x, od)
+            assert gu.max_err(gu.host(od), batch_ref(q[:len(ids)], [kv[i] for i in ids], [lens[i] for i in ids], hq // hkv)) <= tol
+        qn, kn, vn = w.qkv(0, np.arange(60000, 60003))
+        od = torch.full((3, hq, d), float("nan"), device="cuda:0", dtype=qd.dtype)
+        cache.decode_step(0, [0, 1, 2], gu.dev(qn, w), gu.dev(kn, w), gu.dev(vn, w), od)
+        kv2, qr = [], []
+        for b, n in enumerate(lens):
+            pos = np.full((1, 3), n)
+            kv2.append((np.concatenate([kv[b][0], cache.read_kv(b, 0, 0, n, 1).astype(np.float64)]), np.concatenate([kv[b][1], vn[b:b + 1]])))
+            assert gu.max_err(cache.read_kv(b, 0, 0, n, 1), orc.rope(kn[b:b + 1], pos, 0, 1e4, (0, 0, 0))) <= (4e-2 if dtype == "bf16" else 1e-5)
+            assert np.array_equal(cache.read_kv(b, 0, 1, n, 1), vn[b:b + 1])
+            qr.append(orc.rope(qn[b:b + 1], pos, 0, 1e4, (0, 0, 0))[0])
+        assert gu.max_err(gu.host(od), batch_ref(np.stack(qr), kv2, [n + 1 for n in lens], hq // hkv)) <= tol
