@@ -22,10 +22,11 @@ __device__ __forceinline__ float exp_scaled(float d) {
   return fmaf(p, lo, p);
 }
 
-// x / l with inv = 1 / l at hand: the product's remainder corrects it, so that the result is rounded once.
+// x / l with inv = 1 / l at hand: the product's remainder corrects it, so that the result is rounded once.  (An infinite x has
+// none: it stays.)
 __device__ __forceinline__ float quotient(float x, float l, float inv) {
-  const float r = x * inv;
-  return fmaf(fmaf(-r, l, x), inv, r);
+  const float r = x * inv, rest = fmaf(-r, l, x);
+  return rest == rest ? fmaf(rest, inv, r) : r;
 }
 
 // Sum of N registers, pairwise.

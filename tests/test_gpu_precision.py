@@ -94,3 +94,34 @@ def test_bf16_chunk_of_head_dim_64_rounds_its_result_alone(hq, hkv, n_kv, n_q, c
     """Probabilities to 16 bits and more (2^-17 in quadrature with 2^-9.2), sums and partial results in fp32."""
     err, ref = chunk_error("bf16", hq, hkv, 64, n_kv, n_q, causal, splits)
     assert err <= 1.002 * rounded_to_bf16(ref)
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (2, 1, 64)])
+def test_fp32_infinite_value_stays_infinite(hq, hkv, d):
+    """One value of V is infinite: so is the output in that head dim, and no other (one key range and several, few rows and
+    many, one decode row and two)."""
+    lens = [300, 300]
+    w = si.Workload("i", 1, hq, hkv, d, "f32", 2, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, 9990)
+    cache = sv.Cache(1, hq, hkv, d, sv.SV_DTYPE_F32, sv.SV_ROPE_NONE, 1e4, (0, 0, 0), 2, 308, 100)
+    q, k, v = w.qkv(0, np.arange(300))
+    v = v.copy()
+    v[123, 0, 5] = np.inf
+    for s in range(2):
+        cache.append(s, 0, np.zeros(300, np.uint8), None, gu.dev(k, w), gu.dev(v, w))
+    want = np.zeros((hq, d), bool)
+    want[:hq // hkv, 5] = True
+    outs = []
+    for n_q in (100, 3):
+        for splits in (1, 3):
+            print(f"infinite value {hq}/{hkv} x {d} n_q={n_q} splits={splits}", flush=True)
+            cache.set_option(sv.SV_OPT_CHUNK_SPLITS, splits)
+            o = torch.empty(n_q, hq, d, device="cuda:0")
+            cache.attn_chunk(0, 0, gu.dev(q[:n_q], w), o, False)
+            outs.append(o)
+    for ids in ([0], [0, 1]):
+        o = torch.empty(len(ids), hq, d, device="cuda:0")
+        cache.attn_decode(0, ids, gu.dev(q[:len(ids)], w), o)
+        outs.append(o)
+    for o in outs:
+        x = gu.host(o)
+        assert (np.isposinf(x) == want).all() and np.isfinite(x[:, ~want]).all()
