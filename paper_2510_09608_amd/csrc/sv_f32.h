@@ -10,14 +10,15 @@ namespace sv {
 // e^(d / sqrt(D)) of a difference of raw scores (d <= 0, or -infinity).  The exponent d * log2(e) / sqrt(D) is formed in
 // two floats, the product and its rounding error with the rest of the constant, and the second one's factor
 // 2^lo = 1 + lo * ln 2 applied afterwards: rounded to one float, an exponent of -10 puts the weight off by 3e-7.
+// rest: what the score's last addition rounded off, for the low part.
 template <int D>
-__device__ __forceinline__ float exp_scaled(float d) {
+__device__ __forceinline__ float exp_scaled(float d, float rest = 0.f) {
   constexpr double c = 1.4426950408889634074 * (D == 128 ? 0.088388347648318440550 : 0.125);   // log2(e) / sqrt(D)
   constexpr float ch = (float)c, cl = (float)(c - (double)ch);
   const float hi = d * ch;
   // (of -infinity the low part is no number, and the minimum then 1: the weight stays 0.  A d that is no number makes hi,
   // and with it the weight, none either.)
-  const float lo = fminf(fmaf(d, cl, fmaf(d, ch, -hi)) * 0.69314718f, 1.0f);
+  const float lo = fminf(fmaf(rest, ch, fmaf(d, cl, fmaf(d, ch, -hi))) * 0.69314718f, 1.0f);
   const float p = __builtin_amdgcn_exp2f(hi);
   return fmaf(p, lo, p);
 }
@@ -36,13 +37,20 @@ __device__ __forceinline__ float sum_of(const V& v, int at = 0) {
   else return sum_of<N / 2>(v, at) + sum_of<N / 2>(v, at + N / 2);
 }
 
+// What a + b, rounded to sum, leaves.
+template <typename V>
+__device__ __forceinline__ V rest_of(const V& a, const V& b, const V& sum) {
+  const V b2 = sum - a;
+  return (a - (sum - b2)) + (b - b2);
+}
+
 // A running sum in two floats: what an addition rounds off goes into the second one.
 struct Sum {
   float hi = 0.f, lo = 0.f;
   __device__ __forceinline__ void scale(float x) { hi *= x, lo *= x; }
   __device__ __forceinline__ void add(float x) {
-    const float t = hi + x, x2 = t - hi;
-    lo += (hi - (t - x2)) + (x - x2);
+    const float t = hi + x;
+    lo += rest_of(hi, x, t);
     hi = t;
   }
   __device__ __forceinline__ float value() const { return hi + lo; }

@@ -1,7 +1,7 @@
 """How far attention is from 64-bit arithmetic, in the root mean square of the result: what the data types give and no less.
 
 Bound for fp32, in units u = 2^-24 (a rounding is u / sqrt(3) in the mean): a score of head_dim D in chains of L products that
-meet pairwise is off by sqrt(L / 2 + log2(D / L)) roundings, 1.6 u at most (D = 128, L = 8), and its weight by as much; the
+meet pairwise is off by sqrt(L / 2 + log2(D / L)) roundings (one less where the last one is kept), 1.6 u at most (D = 128, L = 8), and its weight by as much; the
 weight itself by half a u; a tile's share of the output (chains of up to 8 keys, pairwise) and up to 20 tiles added one by one
 by sqrt(4 + 2 + 20 / 2) roundings, 2.3 u; key ranges, sums and quotient by another u.  Together 3.0 u; the bound is 3.6."""
 import numpy as np
