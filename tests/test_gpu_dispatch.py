@@ -56,9 +56,11 @@ def test_tokens_of_a_batch_registered_together(dtype, mode):
         _, k, v = w.qkv(0, np.arange(24))
         cache.append(s, 0, np.ones(24, np.uint8), vis, gu.dev(k, w), gu.dev(v, w))
     cache.evict(1, 3, 24, 2)
-    kept = {0: 5 + 24, 1: 5 + 24, 2: 17 + 24}
+    kept, new_k = {0: 5 + 24, 1: 5 + 24, 2: 17 + 24}, {0: [], 1: [], 2: []}
     for step, ids in enumerate(([2, 0, 1], [1, 2], [0, 1, 2])):
         q, k, v = w.qkv(0, np.arange(1000 + 10 * step, 1000 + 10 * step + len(ids)))
+        for s, row in zip(ids, k):
+            new_k[s].append(row)
         q, k, v = gu.dev(q, w), gu.dev(k, w), gu.dev(v, w)
         cache.decode_step(0, ids, q, k, v, torch.empty_like(q))
         print(f"step {step} {ids}", flush=True)
@@ -71,6 +73,8 @@ def test_tokens_of_a_batch_registered_together(dtype, mode):
         assert list(ids[n0:]) == list(range(first, first + n))
         base = n0 if mode == sv.SV_ROPE_1D else n0 - 24 + max(vis)   # a vision block advances by its extent
         assert pos[n0:].tolist() == [[base + i] * 3 for i in range(n)]
+        want = orc.rope(np.stack(new_k[s]), np.asarray(pos[n0:]), mode, 1e4, sec)
+        assert gu.max_err(cache.read_kv(s, 0, 0, n0, n), want) <= (4e-2 if dtype == "bf16" else 1e-5)
 
 
 # ---- head_dim 64 / single precision on the matrix cores ------------------------------------------------------------
