@@ -32,7 +32,7 @@ MEASURED_TRAFFIC = {
     # k_decode_one (key ranges merged in the same launch); evict = k_evict_scan + k_compact (reads + writes, scaled counters)
     "qwen7b_256v_28L": {"attn_chunk": (29.5e6 + 18.1e6) + (18.0e6 + 1.8e6),
                         "decode_sweep": 12.66e6 + 1.52e6,
-                        "evict": (268.2e6 + 262.3e6) + (0.4e6 + 0.3e6)},
+                        "evict": (264.5e6 + 264.2e6) + (0.4e6 + 0.3e6)},
 }
 
 

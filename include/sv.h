@@ -22,6 +22,11 @@
  *     [n][n_kv_heads][head_dim], contiguous, in the cache dtype.
  *   - Query head h reads kv head h / (n_q_heads / n_kv_heads); scores are
  *     scaled by 1/sqrt(head_dim); softmax is accumulated in fp32.
+ *   - bf16 caches: scores, sums and the merge of partial results are fp32.  What
+ *     multiplies V is, at head_dim 128, the probability rounded to bf16 (and long
+ *     chunks' partial results pass through fp16, scaled per row); at head_dim 64
+ *     it keeps 16 bits or more, so that only the result's rounding is left.
+ *     fp32 caches: everything is fp32, sums in short chains.
  */
 #ifndef SV_H_
 #define SV_H_
@@ -68,8 +73,8 @@ typedef struct sv_config {
 } sv_config;
 
 /* sv_config.flags.  SV_FLAG_GENERIC_KERNELS: run the generic (vector ALU) attention kernels and keep
- * the row-major V layout even where the matrix-core kernels apply (bf16, at most 8 query heads per kv head).  Same results to rounding; the parity tests use it to cover the generic kernels
- * on bf16 data.
+ * the row-major V layout even where the matrix-core kernels apply (at most 8 query heads per kv head and 255 kv heads).
+ * Same results to rounding; the parity tests use it to cover the generic kernels (1, 2, 4, 7 or 8 query heads per kv head).
  * SV_FLAG_HOST_LOGIC_ONLY: a test seam.  The cache launches nothing and never touches the arena: argument
  * checks, call-order rules, lengths, retained counts and error codes behave as usual (they are host
  * bookkeeping), attention outputs are not produced, and sv_cache_retained / sv_cache_read_kv return

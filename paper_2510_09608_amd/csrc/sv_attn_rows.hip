@@ -1,7 +1,7 @@
 // Row-wise split-KV attention on the vector ALUs: one query token (all its heads) against a cache
 // prefix, with one row per stream for decode and one row per chunk token for chunk prefill.  The caches of
-// SV_FLAG_GENERIC_KERNELS run it, and those with more than 8 query heads per kv head or more than 255 kv heads where
-// it has an instantiation; all others have matrix-core kernels.
+// SV_FLAG_GENERIC_KERNELS and those with more than 255 kv heads run it, in groups of 1, 2, 4, 7 or 8 query heads per kv
+// head; all others of up to 8 have matrix-core kernels, and larger groups none.
 //
 // The kernel is bound by reading K and V once from HBM: 2 * n_kv_heads *
 // head_dim * esize bytes per cached token per layer, shared by the n_q_heads /
