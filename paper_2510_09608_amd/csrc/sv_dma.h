@@ -24,6 +24,11 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t lane_off, char*
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(lane_off), "s"(bu)
                : "memory", "m0");
 }
+__device__ __forceinline__ uint32_t lds_addr(char* p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)p; }
+// ... with the base known to be uniform and the place in LDS as its address (lds_addr), which costs no scalar instructions per call
+__device__ __forceinline__ void dma16(const void* base, uint32_t lane_off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(lane_off), "s"(base) : "memory", "m0");
+}
 #pragma clang diagnostic pop
 
 }  // namespace sv

@@ -481,3 +481,29 @@ def test_generic_row_kernels_of_every_layout(dtype, hq, hkv, d):
             assert np.array_equal(cache.read_kv(b, 0, 1, n, 1), vn[b:b + 1])
             qr.append(orc.rope(qn[b:b + 1], pos, 0, 1e4, (0, 0, 0))[0])
         assert gu.max_err(gu.host(od), batch_ref(np.stack(qr), kv2, [n + 1 for n in lens], hq // hkv)) <= tol
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(28, 4, 128), (16, 2, 64)])
+@pytest.mark.parametrize("step", [0.9, 6.6, 7.4, 8.2, 9.5])
+def test_chunk_row_maxima_that_rise_by_about_the_allowed_step(hq, hkv, d, step):
+    """Scores that rise from key tile to key tile by about the 8 binary orders for which a row keeps its reference (and by one, so
+    that they add up to it): rows of one tile lie below, at and above the step.  Tile 6 falls back, 200 orders below."""
+    n_kv, n_q = 1100, 150
+    w = si.Workload("r", 1, hq, hkv, d, "bf16", 2, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, 9950)
+    q, k, v = w.qkv(0, np.arange(n_kv))
+    bf16 = lambda x: torch.from_numpy(x).to(torch.bfloat16).float().numpy()   # what the cache holds is what the oracle reads
+    level = np.arange(n_kv) // 64 * step
+    level[6 * 64:7 * 64] -= 200
+    q = bf16(1 + 0.1 * q[n_kv - n_q:])
+    k = bf16((level / (np.sqrt(d) * 1.4427))[:, None, None] + 0.5 * k)
+    cache = sv.Cache(1, hq, hkv, d, sv.SV_DTYPE_BF16, sv.SV_ROPE_NONE, 1e4, (0, 0, 0), 1, n_kv + 8, n_q)
+    cache.append(0, 0, np.zeros(n_kv, np.uint8), None, gu.dev(k, w), gu.dev(v, w))
+    qd = gu.dev(q, w)
+    for causal in (True, False):
+        ref = orc.gqa_attention(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), np.arange(n_kv - n_q, n_kv), causal)
+        for splits in (1, 3):
+            print(f"rising maxima {hq}/{hkv} x {d} step={step} causal={causal} splits={splits}", flush=True)
+            cache.set_option(sv.SV_OPT_CHUNK_SPLITS, splits)
+            od = torch.full_like(qd, float("nan"))
+            cache.attn_chunk(0, 0, qd, od, causal)
+            assert gu.max_err(gu.host(od), ref) <= gu.TOL["bf16"]
