@@ -507,3 +507,18 @@ def test_chunk_row_maxima_that_rise_by_about_the_allowed_step(hq, hkv, d, step):
             od = torch.full_like(qd, float("nan"))
             cache.attn_chunk(0, 0, qd, od, causal)
             assert gu.max_err(gu.host(od), ref) <= gu.TOL["bf16"]
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d,n", [
+    ("bf16", 8, 2, 128, 33 * 128 - 5), ("bf16", 2, 2, 128, 65 * 128 + 3), ("bf16", 4, 2, 64, 66 * 128), ("bf16", 1, 1, 128, 128 * 128),
+    ("bf16", 5, 1, 64, 32 * 128 + 1), ("f32", 8, 2, 128, 34 * 64), ("f32", 2, 1, 64, 66 * 64 + 1), ("f32", 1, 1, 64, 127 * 64)])
+def test_decode_outputs_shared_out_in_finer_units(dtype, hq, hkv, d, n):
+    """Merges of more than 32 and of more than 64 key ranges, whose workgroups take 16 and 8 outputs at a time where there are
+    enough of them: the result, and the same from workgroups that are late."""
+    cache, w, q, k, v = attn_case(dtype, hq, hkv, d, n, 1, True, 9970)
+    ref = orc.gqa_attention(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), np.array([n - 1]), True)
+    for _ in range(2):
+        od = torch.full((1, hq, d), float("nan"), device="cuda:0", dtype=gu.tdtype(w))
+        cache.attn_decode(0, [0], gu.dev(q, w), od)
+        assert gu.max_err(gu.host(od), ref) <= gu.TOL[dtype]
+    test_decode_merge_left_to_late_workgroups(dtype, hq, hkv, d, [n])
