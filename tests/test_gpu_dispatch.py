@@ -522,3 +522,24 @@ def test_decode_outputs_shared_out_in_finer_units(dtype, hq, hkv, d, n):
         cache.attn_decode(0, [0], gu.dev(q, w), od)
         assert gu.max_err(gu.host(od), ref) <= gu.TOL[dtype]
     test_decode_merge_left_to_late_workgroups(dtype, hq, hkv, d, [n])
+
+
+@pytest.mark.parametrize("hq,hkv,d,n", [
+    (12, 12, 128, 2688), (12, 12, 128, 2689), (12, 12, 128, 3040), (12, 12, 128, 3041), (12, 12, 128, 3700), (12, 12, 128, 4300),
+    (12, 12, 128, 4865), (16, 4, 64, 8225), (8, 1, 128, 8193), (8, 1, 128, 10300)])
+def test_decode_key_ranges_between_one_tile_per_wavefront_and_two(hq, hkv, d, n):
+    """Lengths at which a single stream's ranges become 160, 192, 224 and 256 keys long and where that ends: attention alone, then
+    two fused steps, whose token is the last of a range, or one of its own."""
+    cache, w, q, k, v = attn_case("bf16", hq, hkv, d, n, 1, True, 9980)
+    new = [w.qkv(0, np.arange(60000 + i, 60001 + i)) for i in range(2)]
+    for i in range(3):
+        od = torch.full((1, hq, d), float("nan"), device="cuda:0", dtype=torch.bfloat16)
+        if i == 0:
+            cache.attn_decode(0, [0], gu.dev(q, w), od)
+        else:
+            q, kn, vn = new[i - 1]
+            cache.decode_step(0, [0], gu.dev(q, w), gu.dev(kn, w), gu.dev(vn, w), od)
+            k, v = np.concatenate([k, kn]), np.concatenate([v, vn])
+        ref = orc.gqa_attention(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), np.array([n + i - 1]), True)
+        assert gu.max_err(gu.host(od), ref) <= gu.TOL["bf16"]
+    test_decode_merge_left_to_late_workgroups("bf16", hq, hkv, d, [n])
