@@ -87,7 +87,7 @@ Layout make_layout(const sv_config& c) {
   L.n_dev = take(S * 4);
   L.inv_freq = take((size_t)(c.head_dim / 2) * 8);
   L.last_cs = take(S * (size_t)(c.head_dim / 2) * 8);
-  L.cs_tab = take(S * (size_t)c.max_q_tokens * (size_t)(c.head_dim / 2) * 8);
+  L.cs_tab = take(S * ((size_t)c.max_q_tokens + sv::kTextRows) * (size_t)(c.head_dim / 2) * 8);
   L.part_rows = std::max<int64_t>(64 * (int64_t)c.n_streams, std::max<int64_t>(4096, 4 * (int64_t)c.max_q_tokens));
   L.part_o = take((size_t)L.part_rows * c.n_q_heads * c.head_dim * 4);
   L.part_ml = take((size_t)L.part_rows * c.n_q_heads * 4 * 4);   // up to 4 floats per (row, range, head)
@@ -97,7 +97,7 @@ Layout make_layout(const sv_config& c) {
   L.part_dec = take(L.part_dec_bytes);
   L.part_batch_bytes = mfma_eligible(c) ? sv::decode_batch_bytes(c) : 0;   // batches: pieces of up to 256 workgroups
   L.part_batch = take(L.part_batch_bytes);
-  L.scan_agg = take(S * 2 * (sv::kScanMaxWG + 1) * 8);
+  L.scan_agg = take(S * 2 * (sv::kScanWords + 1) * 8);
   L.total = off;
   return L;
 }
@@ -128,12 +128,14 @@ std::vector<std::pair<int64_t, int64_t>> iv_after_evict(
   return out;
 }
 
-// Host bookkeeping of n text tokens registered at the end of a stream (the metadata launch is the caller's).
-void note_text_registered(sv::StreamState& st, int n, bool cs_tab_valid) {
+// Host bookkeeping of n text tokens registered at the end of a stream (the metadata launch is the caller's).  with_vision: by the
+// launch that registered the vision run in front of them.
+void note_text_registered(sv::StreamState& st, int n, bool cs_tab_valid, bool with_vision = false) {
+  st.cs_row0 = with_vision ? st.pending_n : 0;
   st.cs_tab_valid = cs_tab_valid;
   st.pending_slot0 = st.len;
   st.pending_n = n;
-  st.next_parity ^= 1;
+  if (!with_vision) st.next_parity ^= 1;
   st.next_gid += n;
   if (!st.text_iv.empty() && st.text_iv.back().second == st.n_text) st.text_iv.back().second += n;
   else st.text_iv.emplace_back(st.n_text, st.n_text + n);
@@ -146,6 +148,26 @@ void note_text_registered(sv::StreamState& st, int n, bool cs_tab_valid) {
     hipError_t e__ = (expr);                 \
     if (e__ != hipSuccess) return SV_ERR_HIP; \
   } while (0)
+
+// The runs of a second as its eviction registers them: false where the calls behind it refuse one of them or register it
+// otherwise (they then do so themselves, in their order).
+bool runs_of(const sv_cache* c, const sv::StreamState& st, const sv_chunk_io* io, int64_t n_kept, sv::NewRuns& r) {
+  if (!(c->use_mfma || c->f32_mfma) || io->decode_layers_batched) return false;
+  if (io->n_vision < 1 || io->n_vision > c->cfg.max_q_tokens || io->n_text > sv::kTextRows) return false;
+  if (n_kept + io->n_vision + io->n_text > c->cfg.capacity_tokens) return false;
+  const int32_t* g = io->grid_thw;
+  const bool has_grid = g[0] > 0 || g[1] > 0 || g[2] > 0;
+  if (has_grid) {
+    for (int i = 0; i < 3; ++i)
+      if (g[i] < 1 || g[i] > 32767) return false;
+    if ((int64_t)g[0] * g[1] * g[2] != io->n_vision) return false;
+  } else if (c->cfg.rope_mode == SV_ROPE_3D) {
+    return false;
+  }
+  const bool has_blk = has_grid && c->cfg.rope_mode == SV_ROPE_3D;
+  r = {io->n_vision, io->n_text, (int)n_kept, has_blk ? st.next_blk : -1, g[0], g[1], g[2], st.next_gid, st.n_vis, st.n_text};
+  return true;
+}
 
 // Device work of a call: skipped for a cache created with SV_FLAG_HOST_LOGIC_ONLY.
 #define SV_DEV(expr)                 \
@@ -212,6 +234,7 @@ int sv_cache_create(const sv_config* cfg, void* dev_arena, size_t arena_bytes, v
   c->inv_freq = (double*)(base + L.inv_freq);
   c->last_cs = (float2*)(base + L.last_cs);
   c->cs_tab = (float2*)(base + L.cs_tab);
+  c->cs_rows = (int64_t)cfg->max_q_tokens + sv::kTextRows;
   c->part_o = (float*)(base + L.part_o);
   c->part_ml = (float*)(base + L.part_ml);
   c->part_rows = L.part_rows;
@@ -242,7 +265,7 @@ int sv_cache_create(const sv_config* cfg, void* dev_arena, size_t arena_bytes, v
   if (e == hipSuccess) e = hipMemsetAsync(c->counters, 0, (size_t)L.part_rows * cfg->n_kv_heads * 4, s);
   if (e == hipSuccess && L.part_dec_bytes > 0) e = hipMemsetAsync(c->part_dec, 0, L.part_dec_bytes, s);
   if (e == hipSuccess && L.part_batch_bytes > 0) e = hipMemsetAsync(c->part_batch, 0, L.part_batch_bytes, s);
-  if (e == hipSuccess) e = hipMemsetAsync(c->scan_agg, 0, (size_t)cfg->n_streams * 2 * (sv::kScanMaxWG + 1) * 8, s);
+  if (e == hipSuccess) e = hipMemsetAsync(c->scan_agg, 0, (size_t)cfg->n_streams * 2 * (sv::kScanWords + 1) * 8, s);
   // blocked V^T: slots past a stream's end inside its last block are multiplied by probabilities of zero and must
   // never hold NaN patterns, so the store starts out cleared
   if (e == hipSuccess && c->v_blocked)
@@ -280,10 +303,11 @@ int sv_cache_len(sv_cache* c, int stream_id, int64_t* n_out) {
 }
 
 // sv_cache_append, with the option of leaving the K/V store to the caller (sv_stream_step stores a chunk's K and V and
-// rotates its Q in one launch of its own): all checks and bookkeeping are the same.
+// rotates its Q in one launch of its own), and of a run that the eviction has registered already: all checks and bookkeeping
+// are the same.
 static int append_impl(sv_cache* c, int stream_id, int layer, int n, const uint8_t* types_host,
                        const int32_t* grid_thw_host, const void* k_dev, const void* v_dev,
-                       int64_t* slot0_out, void* hip_stream, bool launch_kv) {
+                       int64_t* slot0_out, void* hip_stream, bool launch_kv, bool registered = false) {
   if (!stream_ok(c, stream_id) || layer < 0 || layer >= c->cfg.n_layers || n < 0) return SV_ERR_INVALID;
   sv::StreamState& st = c->st[stream_id];
   hipStream_t s = (hipStream_t)hip_stream;
@@ -324,15 +348,17 @@ static int append_impl(sv_cache* c, int stream_id, int layer, int n, const uint8
     // the cos/sin of a run of at most max_q_tokens tokens are kept: every layer's K store, sv_rope_apply and, in
     // sv_stream_step, the attention kernel's Q rotation read them instead of evaluating sincos again
     const bool with_cs = c->cfg.rope_mode != SV_ROPE_NONE && n <= c->cfg.max_q_tokens;
-    SV_DEV(sv::launch_meta_append(c, stream_id, st.next_parity, st.len, n, st.next_gid, st.n_text,
-                                  st.n_vis, type_uniform, type_uniform < 0 ? &mask : nullptr,
-                                  has_blk ? st.next_blk : -1, gT, gH, gW, with_cs, s));
-    st.cs_tab_valid = with_cs;
+    if (!registered) {
+      SV_DEV(sv::launch_meta_append(c, stream_id, st.next_parity, st.len, n, st.next_gid, st.n_text,
+                                    st.n_vis, type_uniform, type_uniform < 0 ? &mask : nullptr,
+                                    has_blk ? st.next_blk : -1, gT, gH, gW, with_cs, s));
+      st.next_parity ^= 1;
+    }
+    st.cs_tab_valid = with_cs, st.cs_row0 = 0;
     st.pending_slot0 = st.len;
     st.pending_n = n;
     if (launch_kv) SV_DEV(sv::launch_store_tokens(c, stream_id, 0, st.len, n, nullptr, k_dev, v_dev, s));
 
-    st.next_parity ^= 1;
     if (has_blk) st.next_blk++;
     st.next_gid += n;
     if (st.len == st.front && st.n_text == st.front)   // the cache is the opening text run so far: it may grow
@@ -368,8 +394,10 @@ int sv_cache_append(sv_cache* c, int stream_id, int layer, int n, const uint8_t*
   return append_impl(c, stream_id, layer, n, types_host, grid_thw_host, k_dev, v_dev, slot0_out, hip_stream, true);
 }
 
-int sv_cache_evict(sv_cache* c, int stream_id, int64_t n_sink, int64_t vision_window,
-                   int64_t text_window, int64_t* n_retained_out, void* hip_stream) {
+// sv_cache_evict; io (may be NULL): the second that follows, whose two runs are registered along with the eviction if there is
+// one and they can be (registered_out: whether they were).
+static int evict_impl(sv_cache* c, int stream_id, int64_t n_sink, int64_t vision_window, int64_t text_window,
+                      int64_t* n_retained_out, void* hip_stream, const sv_chunk_io* io, bool* registered_out) {
   if (!stream_ok(c, stream_id)) return SV_ERR_INVALID;
   if (n_sink < 0 || vision_window < SV_WINDOW_INF || text_window < SV_WINDOW_INF) return SV_ERR_INVALID;
   sv::StreamState& st = c->st[stream_id];
@@ -392,7 +420,10 @@ int sv_cache_evict(sv_cache* c, int stream_id, int64_t n_sink, int64_t vision_wi
   // place as well is already in the half this one fills.
   const int64_t gone = (n_sink < st.front && text_lo > n_sink) ? n_sink : st.front;
   const int64_t n_still = std::min(st.still[st.cur], gone);
-  SV_DEV(sv::launch_evict_scan(c, stream_id, st.next_parity, st.len, n_sink, text_lo, vis_lo, s));
+  sv::NewRuns runs;
+  const bool registers = io && runs_of(c, st, io, n_new, runs);
+  if (registered_out) *registered_out = registers;
+  SV_DEV(sv::launch_evict_scan(c, stream_id, st.next_parity, st.len, n_sink, text_lo, vis_lo, registers ? &runs : nullptr, s));
   if (n_new > 0) SV_DEV(sv::launch_compact(c, stream_id, n_new, n_still, s));
   st.still[st.cur ^ 1] = gone;
   st.front = gone;
@@ -406,6 +437,11 @@ int sv_cache_evict(sv_cache* c, int stream_id, int64_t n_sink, int64_t vision_wi
   st.pending_n = 0;
   st.cs_tab_valid = false;
   return SV_OK;
+}
+
+int sv_cache_evict(sv_cache* c, int stream_id, int64_t n_sink, int64_t vision_window,
+                   int64_t text_window, int64_t* n_retained_out, void* hip_stream) {
+  return evict_impl(c, stream_id, n_sink, vision_window, text_window, n_retained_out, hip_stream, nullptr, nullptr);
 }
 
 int sv_rope_apply(sv_cache* c, int stream_id, int64_t slot0, int n, void* q_dev_inout,
@@ -536,7 +572,8 @@ int sv_stream_step(sv_cache* c, int stream_id, int64_t n_sink, int64_t vision_wi
   if (io->n_text > 0 && (!io->q_text || !io->k_text || !io->v_text || !io->o_text)) return SV_ERR_INVALID;
   const int L = c->cfg.n_layers;
   const size_t qrow = (size_t)c->cfg.n_q_heads * c->row_bytes, kvrow = (size_t)c->cfg.n_kv_heads * c->row_bytes;
-  int rc = sv_cache_evict(c, stream_id, n_sink, vision_window, text_window, n_retained_out, hip_stream);
+  bool registered = false;   // both runs, by the eviction
+  int rc = evict_impl(c, stream_id, n_sink, vision_window, text_window, n_retained_out, hip_stream, io, &registered);
   if (rc != SV_OK) return rc;
   if (io->n_vision > 0) {
     const int n = io->n_vision;
@@ -551,7 +588,7 @@ int sv_stream_step(sv_cache* c, int stream_id, int64_t n_sink, int64_t vision_wi
       const char* v = (const char*)io->v_vision + (size_t)l * n * kvrow;
       char* o = (char*)io->o_vision + (size_t)l * n * qrow;
       rc = append_impl(c, stream_id, l, n, types.data(), has_grid ? io->grid_thw : nullptr, k, v, &slot0, hip_stream,
-                       !fused);
+                       !fused, registered);
       if (rc != SV_OK) return rc;
       if (fused && c->f32_mfma) {
         SV_DEV(sv::launch_store_tokens(c, stream_id, l, slot0, n, q, k, v, (hipStream_t)hip_stream));
@@ -586,7 +623,7 @@ int sv_stream_step(sv_cache* c, int stream_id, int64_t n_sink, int64_t vision_wi
     }
     return SV_OK;
   }
-  if ((c->use_mfma || c->f32_mfma) && io->n_text > 1 && io->n_text <= c->cfg.max_q_tokens) {
+  if (registered ? io->n_text > 0 : (c->use_mfma || c->f32_mfma) && io->n_text > 1 && io->n_text <= c->cfg.max_q_tokens) {
     // The call names its n_text decode steps in advance, and what a decoded text token's registration writes (arrival
     // id, rank, position, rotary cos/sin) does not depend on the token: the run is registered ONCE, as an append of
     // n_text text tokens whose K/V arrive later, and the fused decode launch of step t stores token t and attends to
@@ -599,9 +636,10 @@ int sv_stream_step(sv_cache* c, int stream_id, int64_t n_sink, int64_t vision_wi
     if (st.len + n > c->cfg.capacity_tokens) return SV_ERR_CAPACITY;
     const int64_t len0 = st.len;
     const bool with_cs = c->cfg.rope_mode != SV_ROPE_NONE;
-    SV_DEV(sv::launch_meta_append(c, stream_id, st.next_parity, len0, n, st.next_gid, st.n_text, st.n_vis, SV_TEXT, nullptr,
-                                  -1, 0, 0, 0, with_cs, (hipStream_t)hip_stream));
-    note_text_registered(st, n, with_cs);
+    if (!registered)
+      SV_DEV(sv::launch_meta_append(c, stream_id, st.next_parity, len0, n, st.next_gid, st.n_text, st.n_vis, SV_TEXT, nullptr,
+                                    -1, 0, 0, 0, with_cs, (hipStream_t)hip_stream));
+    note_text_registered(st, n, with_cs, registered);
     for (int t = 0; t < n; ++t)
       for (int l = 0; l < L; ++l) {
         const size_t i = (size_t)t * L + l;

@@ -16,7 +16,9 @@ namespace sv {
 // holds keys [8 b, 8 b + 8) as [head dim][key 0..7] (2 KB at head_dim 128), element (key, d) at vt_elem(key, d).  A
 // block row is exactly the 16-byte piece a lane wants; 32- and 64-key tiles are 4 and 8 consecutive blocks; and a
 // compaction that drops runs of 8 k tokens moves whole blocks.
-constexpr int kScanMaxWG = 128;   // workgroups of one eviction scan
+constexpr int kScanMaxWG = 128;   // workgroups of one eviction scan that have tokens
+constexpr int kScanMaxReg = 64;   // ... that register new ones
+constexpr int kScanWords = kScanMaxWG + kScanMaxReg;
 constexpr int kVB = 8;
 template <int D>
 __host__ __device__ inline size_t vt_elem(int64_t key, int d) {
@@ -51,7 +53,8 @@ struct StreamState {
   std::vector<int64_t> layer_len;                    // tokens stored per layer
   int64_t pending_slot0 = 0;                         // first slot of the append in flight
   int pending_n = 0;
-  bool cs_tab_valid = false;                         // cs_tab holds the rotary cos/sin of the pending run's tokens
+  bool cs_tab_valid = false;                         // cs_tab holds the rotary cos/sin of the pending run's tokens,
+  int cs_row0 = 0;                                   // from this row of the stream's part on
   // Slots [0, front) hold the text tokens of rank 0 .. front - 1: the stream's opening text run (system prompt and
   // what follows it before the first vision token), as far as evictions have left it in place.  An eviction leaves
   // the slots below the run's first leaving token where they are, unshifted; still[h] is that bound for the eviction
@@ -92,8 +95,9 @@ struct sv_cache {
   int32_t* n_dev;            // device [n_streams]             retained count written by the scan
   double* inv_freq;          // device [head_dim/2]
   float2* last_cs;           // device [n_streams][head_dim/2]  cos/sin at the position of the newest token
-  float2* cs_tab;            // device [n_streams][max_q_tokens][head_dim/2]  cos/sin of the tokens of the last
+  float2* cs_tab;            // device [n_streams][cs_rows][head_dim/2]  cos/sin of the tokens of the last
                              // registered run (written when it has at most max_q_tokens tokens)
+  int64_t cs_rows;           // max_q_tokens + kTextRows
   float* part_o;             // device split-KV partial outputs
   float* part_ml;            // device split-KV partial (max, sum)
   int64_t part_rows;         // capacity of the partial buffers in (token, split) pairs
@@ -101,7 +105,7 @@ struct sv_cache {
   unsigned long long* part_batch; // device: the same for the batches of bf16 caches
   unsigned long long* part_dec;   // device: marked partial results of a single stream's key ranges in the matrix-core
                                   // decode kernel (zero at create and between launches; sv_attn_decode.hip)
-  unsigned long long* scan_agg;   // device [n_streams][kScanMaxWG + 1][2]: tagged totals of the eviction scan's
+  unsigned long long* scan_agg;   // device [n_streams][kScanWords + 1][2]: tagged totals of the eviction scan's
                                   // workgroups, then the scan's launch tag (zero at create, written by nothing else;
                                   // sv_meta.hip)
   bool host_logic_only = false;   // created with SV_FLAG_HOST_LOGIC_ONLY: no device work, bookkeeping only
@@ -112,6 +116,8 @@ struct sv_cache {
   std::vector<sv::StreamState> st;
   mutable sv::ChunkPlan chunk_plan, store_plan;   // host only; a handle is used by one thread at a time
 
+  // cos/sin of the pending run's tokens
+  float2* run_cs(int stream) const { return cs_tab + ((size_t)stream * cs_rows + st[stream].cs_row0) * (cfg.head_dim / 2); }
   char* kv_ptr(int stream, int half, int layer, int which) const {
     return kv_base + (size_t)stream * stream_kv_stride + (size_t)half * half_stride +
            (size_t)layer * layer_stride + (size_t)which * tensor_stride;
@@ -138,9 +144,17 @@ hipError_t launch_meta_append(const sv_cache* c, int stream, int next_parity, in
 // The same for one new text token (slot = the stream's length) of each of n_list distinct streams, in one launch.
 hipError_t launch_meta_tokens(const sv_cache* c, const int32_t* streams, int n_list, hipStream_t s);
 
-// Keep rule: text rank < n_sink or rank >= text_lo; vision rank >= vis_lo.
+// A second's two runs, registered by the eviction in front of them: n_vision vision tokens of one grid behind the n_kept
+// survivors, then n_text text tokens, at most kTextRows, whose cos/sin rows follow the vision tokens' in cs_tab.
+constexpr int kTextRows = 64;
+struct NewRuns {
+  int n_vision, n_text, n_kept, blk, gT, gH, gW;   // blk < 0: without a grid
+  int64_t gid0, rank_vis0, rank_text0;
+};
+
+// Keep rule: text rank < n_sink or rank >= text_lo; vision rank >= vis_lo.  runs (may be NULL): registered as well.
 hipError_t launch_evict_scan(const sv_cache* c, int stream, int next_parity, int64_t n_old,
-                             int64_t n_sink, int64_t text_lo, int64_t vis_lo, hipStream_t s);
+                             int64_t n_sink, int64_t text_lo, int64_t vis_lo, const NewRuns* runs, hipStream_t s);
 
 // Slots below `n_still` (rounded down to the kernel's token group) are not moved: the caller knows that the other half
 // already holds them.

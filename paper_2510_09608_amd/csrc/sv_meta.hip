@@ -9,6 +9,46 @@
 namespace sv {
 namespace {
 
+// cos/sin of a rotary angle, as the row movers compute them: angle in double, for bf16 data sincosf of its float value
+__device__ __forceinline__ float2 angle_cs(int p, double freq, int f32_data) {
+  const double ang = (double)p * freq;
+  float2 cs;
+  if (f32_data) {
+    double sd, cd;
+    sincos(ang, &sd, &cd);
+    cs = make_float2((float)cd, (float)sd);
+  } else {
+    sincosf((float)ang, &cs.y, &cs.x);
+  }
+  return cs;
+}
+// metadata of token j of a run that begins at `slot0`; next: the scalar position counter before the run
+__device__ __forceinline__ void write_token(const MetaPtrs& m, int64_t slot0, int j, int next, int type, int64_t gid, int64_t rank,
+                                            int rope3d, int blk, int gT, int gH, int gW) {
+  const int64_t slot = slot0 + j;
+  m.gid[slot] = gid;
+  m.rank[slot] = rank;
+  m.type[slot] = (uint8_t)type;
+  if (rope3d && blk >= 0) {
+    const int lt = j / (gH * gW), lh = (j / gW) % gH, lw = j % gW;
+    m.blk[slot] = blk;
+    m.local4[slot] = make_short4((short)lt, (short)lh, (short)lw, (short)max(gT, max(gH, gW)));
+    m.pos4[slot] = make_int4(next + lt, next + lh, next + lw, next);
+  } else {
+    const int p = rope3d ? next + j : (int)slot;
+    m.blk[slot] = -1;
+    m.local4[slot] = make_short4(0, 0, 0, 1);
+    m.pos4[slot] = make_int4(p, p, p, p);
+  }
+}
+// the position that pair i of token j of the run turns by
+__device__ __forceinline__ int angle_pos(int64_t slot0, int j, int i, int next, int rope3d, int blk, int gH, int gW, int s0, int s01) {
+  if (!rope3d) return (int)(slot0 + j);   // 1-D: position == slot
+  if (blk < 0) return next + j;
+  const int lt = j / (gH * gW), lh = (j / gW) % gH, lw = j % gW;
+  return next + (i < s0 ? lt : (i < s01 ? lh : lw));
+}
+
 // ---------------------------------------------------------------------------------
 // New tokens: slot, arrival id, rank within type, block coordinates and position.
 // The scalar position counter lives in device memory as a two-entry ping-pong
@@ -24,44 +64,15 @@ __global__ void k_meta_append(MetaPtrs m, const int32_t* __restrict__ next_in, i
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   const int next = *next_in;
   if (cs_tab != nullptr && j < n * half) {
-    // cos/sin of every new token's rotary angles (thread = one token, one frequency), as the row movers compute
-    // them: angle in double, for bf16 data sincosf of its float value
+    // cos/sin of every new token's rotary angles (thread = one token, one frequency)
     const int tok = j / half, i = j % half;
-    int p;
-    if (rope3d && blk >= 0) {
-      const int lt = tok / (gH * gW), lh = (tok / gW) % gH, lw = tok % gW;
-      p = next + (i < s0 ? lt : (i < s01 ? lh : lw));
-    } else {
-      p = rope3d ? next + tok : (int)(slot0 + tok);
-    }
-    const double ang = (double)p * inv_freq[i];
-    float2 cs;
-    if (f32_data) {
-      double sd, cd;
-      sincos(ang, &sd, &cd);
-      cs = make_float2((float)cd, (float)sd);
-    } else {
-      sincosf((float)ang, &cs.y, &cs.x);
-    }
-    cs_tab[j] = cs;
+    cs_tab[j] = angle_cs(angle_pos(slot0, tok, i, next, rope3d, blk, gH, gW, s0, s01), inv_freq[i], f32_data);
   }
   if (blockIdx.x == 0 && threadIdx.x < half) {
     // cos/sin of the rotary angles of the LAST token of this append (the decode kernel's query token)
     const int i = threadIdx.x;
-    int pt, ph, pw;
-    if (rope3d && blk >= 0) pt = next + gT - 1, ph = next + gH - 1, pw = next + gW - 1;
-    else pt = ph = pw = rope3d ? next + n - 1 : (int)(slot0 + n - 1);
-    const int p = !rope3d ? pt : (i < s0 ? pt : (i < s01 ? ph : pw));
-    const double ang = rope_none ? 0.0 : (double)p * inv_freq[i];
-    float2 cs;
-    if (f32_data) {
-      double sd, cd;
-      sincos(ang, &sd, &cd);
-      cs = make_float2((float)cd, (float)sd);
-    } else {
-      sincosf((float)ang, &cs.y, &cs.x);
-    }
-    last_cs[i] = cs;
+    last_cs[i] = rope_none ? make_float2(1.f, 0.f)
+                           : angle_cs(angle_pos(slot0, n - 1, i, next, rope3d, blk, gH, gW, s0, s01), inv_freq[i], f32_data);
   }
   if (j == 0) {
     int adv;
@@ -84,21 +95,7 @@ __global__ void k_meta_append(MetaPtrs m, const int32_t* __restrict__ next_in, i
     vis_before += __popc(mask.w[j >> 5] & ((1u << (j & 31)) - 1u));
     rank = type == SV_VISION ? rank_vis0 + vis_before : rank_text0 + (j - vis_before);
   }
-  const int64_t slot = slot0 + j;
-  m.gid[slot] = gid0 + j;
-  m.rank[slot] = rank;
-  m.type[slot] = (uint8_t)type;
-  if (rope3d && blk >= 0) {
-    const int lt = j / (gH * gW), lh = (j / gW) % gH, lw = j % gW;
-    m.blk[slot] = blk;
-    m.local4[slot] = make_short4((short)lt, (short)lh, (short)lw, (short)max(gT, max(gH, gW)));
-    m.pos4[slot] = make_int4(next + lt, next + lh, next + lw, next);
-  } else {
-    const int p = rope3d ? next + j : (int)slot;
-    m.blk[slot] = -1;
-    m.local4[slot] = make_short4(0, 0, 0, 1);
-    m.pos4[slot] = make_int4(p, p, p, p);
-  }
+  write_token(m, slot0, j, next, type, gid0 + j, rank, rope3d, blk, gT, gH, gW);
 }
 
 // ---------------------------------------------------------------------------------
@@ -124,16 +121,7 @@ __global__ __launch_bounds__(64) void k_meta_tokens(MetaPtrs m0, MetaPtrs m1, in
   const int next = next_pos[2 * sid + parity];
   const int p = rope3d ? next : r.slot;   // 1-D: position == slot
   if (lane < half) {
-    const double ang = rope_none ? 0.0 : (double)p * inv_freq[lane];
-    float2 cs;
-    if (f32_data) {
-      double sd, cd;
-      sincos(ang, &sd, &cd);
-      cs = make_float2((float)cd, (float)sd);
-    } else {
-      sincosf((float)ang, &cs.y, &cs.x);
-    }
-    last_cs[(size_t)sid * half + lane] = cs;
+    last_cs[(size_t)sid * half + lane] = rope_none ? make_float2(1.f, 0.f) : angle_cs(p, inv_freq[lane], f32_data);
   }
   if (lane == 0) {
     const bool second = (r.stream & 2) != 0;
@@ -184,6 +172,11 @@ __global__ __launch_bounds__(64) void k_meta_tokens(MetaPtrs m0, MetaPtrs m1, in
 // for the sums and the scan (each step a round trip of 100 cycles) and a 512-byte table row per token, 64 of them one after
 // the other, it took 11 to 13 us at 5 to 18 thousand tokens and 7 at 60; this way 5.3 to 6.2 and 3.2.
 // At most kScanMaxWG workgroups: longer caches take several passes per workgroup.
+//
+// Registration.  A second's eviction is followed by the registration of its vision and of its text tokens, which needs nothing
+// from it but the position counter.  Where the caller knows them (sv_stream_step), `n_reg` more workgroups without tokens of their
+// own, behind the others, wait for the totals as those do and write what k_meta_append would have, in two launches (the smallest
+// second, fp32, 1 layer, 16 + 4 tokens, where every launch is 3 to 4 us of the host: 42.9 -> 38.9 us).
 // ---------------------------------------------------------------------------------
 constexpr int kScanThreads = 256;
 constexpr int kScanWaves = kScanThreads / 64;
@@ -212,13 +205,16 @@ __global__ __launch_bounds__(kScanThreads) void k_evict_scan(MetaPtrs in, MetaPt
                                                              int f32_data, int32_t* __restrict__ next_out,
                                                              int32_t* __restrict__ n_out, int n_old, int64_t n_sink,
                                                              int64_t text_lo, int64_t vis_lo, int passes,
-                                                             unsigned long long* agg) {
+                                                             unsigned long long* agg, int n_reg, NewRuns runs, int rope3d, int s0,
+                                                             int s01, float2* __restrict__ cs_tab,
+                                                             float2* __restrict__ last_cs) {
   __shared__ int2 sh_pass[kScanWaves], sh_all[kScanWaves], sh_carry[kScanWaves];   // {kept tokens, advance}
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int w = blockIdx.x, span = passes * kScanThreads;
   const int first = w * span;
-  const uint32_t tag_old = (uint32_t)agg[2 * kScanMaxWG];   // written by the launch before this one
+  const uint32_t tag_old = (uint32_t)agg[2 * kScanWords];   // written by the launch before this one
   const double my_freq = dtab != nullptr && lane < half ? inv_freq[lane] : 0.0;
+  const bool registers = w >= (int)gridDim.x - n_reg;
 
   // The token and its successor (the look-ahead for "last of its block").  Indices are clamped instead of guarded
   // and the rule below is written without short-circuits, so that every load is unconditional and all nine go out
@@ -319,7 +315,7 @@ __global__ __launch_bounds__(kScanThreads) void k_evict_scan(MetaPtrs in, MetaPt
   }
 
   // ---- 3. and 4. own tokens on top of the carry, survivors out, table rows
-  for (int p = 0; p < passes; ++p) {
+  for (int p = 0; p < passes && !registers; ++p) {
     const int i = first + p * kScanThreads + tid;
     ScanTok t = t0;
     bool keep = keep0;
@@ -383,13 +379,41 @@ __global__ __launch_bounds__(kScanThreads) void k_evict_scan(MetaPtrs in, MetaPt
     }
     if (keep) turn[d] = row;
   }
+  // ---- registration: the scalar position counter is the sum of all advances
+  const int adv_vis = rope3d && runs.blk >= 0 ? max(runs.gT, max(runs.gH, runs.gW)) : runs.n_vision;
+  if (registers) {
+    const int n_new = runs.n_vision + runs.n_text, next_text = run_adv + adv_vis;
+    const int64_t slot_text = (int64_t)runs.n_kept + runs.n_vision;
+    const int at = (w - ((int)gridDim.x - n_reg)) * kScanThreads + tid, step = n_reg * kScanThreads;
+    auto cs_of = [&](int j, int i) {
+      const bool vis = j < runs.n_vision;
+      const int p = vis ? angle_pos(runs.n_kept, j, i, run_adv, rope3d, runs.blk, runs.gH, runs.gW, s0, s01)
+                        : angle_pos(slot_text, j - runs.n_vision, i, next_text, rope3d, -1, 1, 1, s0, s01);
+      return angle_cs(p, inv_freq[i], f32_data);
+    };
+    for (int j = at; j < n_new; j += step) {
+      if (j < runs.n_vision)
+        write_token(out, runs.n_kept, j, run_adv, SV_VISION, runs.gid0 + j, runs.rank_vis0 + j, rope3d, runs.blk, runs.gT, runs.gH, runs.gW);
+      else
+        write_token(out, slot_text, j - runs.n_vision, next_text, SV_TEXT, runs.gid0 + j, runs.rank_text0 + (j - runs.n_vision), rope3d,
+                    -1, 1, 1, 1);
+    }
+    if (dtab != nullptr)
+      for (int x = at; x < n_new * half; x += step) {
+        const float2 cs = cs_of(x / half, x % half);
+        cs_tab[x] = cs;
+        if (x / half == n_new - 1) last_cs[x % half] = cs;
+      }
+    else if (at < half)
+      last_cs[at] = make_float2(1.f, 0.f);
+  }
   if (w == (int)gridDim.x - 1) {
     if (tid == 0) {
-      *next_out = run_adv;
-      *n_out = run_cnt;
-      agg[2 * kScanMaxWG] = tag;
+      *next_out = n_reg > 0 ? run_adv + adv_vis + runs.n_text : run_adv;
+      *n_out = n_reg > 0 ? run_cnt + runs.n_vision + runs.n_text : run_cnt;
+      agg[2 * kScanWords] = tag;
     }
-    for (int b = (int)gridDim.x + tid; b < kScanMaxWG; b += kScanThreads) agg[2 * b] = 0ull, agg[2 * b + 1] = 0ull;
+    for (int b = (int)gridDim.x + tid; b < kScanWords; b += kScanThreads) agg[2 * b] = 0ull, agg[2 * b + 1] = 0ull;
   }
 }
 
@@ -412,7 +436,7 @@ hipError_t launch_meta_append(const sv_cache* c, int stream, int next_parity, in
                      c->last_cs + (size_t)stream * half, c->inv_freq, half, c->cfg.rope_mode == SV_ROPE_NONE ? 1 : 0,
                      c->cfg.mrope_sections[0], c->cfg.mrope_sections[0] + c->cfg.mrope_sections[1],
                      c->cfg.dtype == SV_DTYPE_F32 ? 1 : 0, c->n_dev + stream,
-                     with_cs_tab ? c->cs_tab + (size_t)stream * c->cfg.max_q_tokens * half : nullptr);
+                     with_cs_tab ? c->cs_tab + (size_t)stream * c->cs_rows * half : nullptr);
   return hipGetLastError();
 }
 
@@ -436,7 +460,7 @@ hipError_t launch_meta_tokens(const sv_cache* c, const int32_t* streams, int n_l
 }
 
 hipError_t launch_evict_scan(const sv_cache* c, int stream, int next_parity, int64_t n_old, int64_t n_sink,
-                             int64_t text_lo, int64_t vis_lo, hipStream_t s) {
+                             int64_t text_lo, int64_t vis_lo, const NewRuns* runs, hipStream_t s) {
   const size_t off = (size_t)stream * (size_t)c->cfg.capacity_tokens;
   const int cur = c->st[stream].cur;
   MetaPtrs in = c->meta[cur], out = c->meta[cur ^ 1];
@@ -444,13 +468,17 @@ hipError_t launch_evict_scan(const sv_cache* c, int stream, int next_parity, int
   out.gid += off, out.rank += off, out.pos4 += off, out.local4 += off, out.blk += off, out.type += off;
   const int half = c->cfg.head_dim / 2;
   const int tiles = (int)((n_old + kScanThreads - 1) / kScanThreads);
+  // two cos/sin per thread of the registering workgroups
+  const int n_reg = runs ? std::max(1, std::min(kScanMaxReg, ((runs->n_vision + runs->n_text) * half + 2 * kScanThreads - 1) / (2 * kScanThreads))) : 0;
   const int passes = (tiles + kScanMaxWG - 1) / kScanMaxWG;
   const int wgs = (tiles + passes - 1) / passes;
-  unsigned long long* agg = c->scan_agg + (size_t)stream * 2 * (kScanMaxWG + 1);
-  hipLaunchKernelGGL(k_evict_scan, dim3(wgs), dim3(kScanThreads), 0, s, in, out, c->src + off, c->turn + off,
+  unsigned long long* agg = c->scan_agg + (size_t)stream * 2 * (kScanWords + 1);
+  hipLaunchKernelGGL(k_evict_scan, dim3(wgs + n_reg), dim3(kScanThreads), 0, s, in, out, c->src + off, c->turn + off,
                      c->cfg.rope_mode != SV_ROPE_NONE ? c->dtab + off * half : nullptr, c->inv_freq, half,
                      c->cfg.dtype == SV_DTYPE_F32 ? 1 : 0, c->next_pos + 2 * stream + (next_parity ^ 1), c->n_dev + stream, (int)n_old, n_sink, text_lo,
-                     vis_lo, passes, agg);
+                     vis_lo, passes, agg, n_reg, runs ? *runs : NewRuns{}, c->cfg.rope_mode == SV_ROPE_3D ? 1 : 0, c->cfg.mrope_sections[0],
+                     c->cfg.mrope_sections[0] + c->cfg.mrope_sections[1], c->cs_tab + (size_t)stream * c->cs_rows * half,
+                     c->last_cs + (size_t)stream * half);
   return hipGetLastError();
 }
 

@@ -474,7 +474,7 @@ __global__ __launch_bounds__(256) void k_compact(const T* __restrict__ old_base,
 const float2* run_table(const sv_cache* c, int stream, int64_t slot0, int n) {
   const StreamState& st = c->st[stream];
   if (!st.cs_tab_valid || st.pending_slot0 != slot0 || st.pending_n != n) return nullptr;
-  return c->cs_tab + (size_t)stream * c->cfg.max_q_tokens * (c->cfg.head_dim / 2);
+  return c->run_cs(stream);
 }
 
 template <typename T, int D>

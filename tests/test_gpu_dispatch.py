@@ -543,3 +543,51 @@ def test_decode_key_ranges_between_one_tile_per_wavefront_and_two(hq, hkv, d, n)
         ref = orc.gqa_attention(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), np.array([n + i - 1]), True)
         assert gu.max_err(gu.host(od), ref) <= gu.TOL["bf16"]
     test_decode_merge_left_to_late_workgroups("bf16", hq, hkv, d, [n])
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d,mode", [
+    ("bf16", 4, 2, 128, sv.SV_ROPE_3D), ("bf16", 4, 4, 64, sv.SV_ROPE_1D), ("f32", 2, 1, 64, sv.SV_ROPE_3D),
+    ("f32", 4, 2, 128, sv.SV_ROPE_1D), ("bf16", 4, 2, 64, sv.SV_ROPE_NONE)])
+@pytest.mark.parametrize("budgets", [(5, 30, 9), (0, 0, 0), (70, 300, 0), (3, 1000, 1000)])
+def test_runs_registered_by_the_eviction(dtype, hq, hkv, d, mode, budgets):
+    """Seconds through sv_stream_step, whose eviction registers both runs, against the calls one by one: ids, positions, every
+    stored row, outputs, and the rotation of the newest run's queries afterwards.  Text runs of none, one, as many as are registered
+    that way and one more; grids of all extents and none; evictions that leave nothing and that do nothing."""
+    sec = ((16, 24, 24) if d == 128 else (8, 12, 12)) if mode == sv.SV_ROPE_3D else (0, 0, 0)
+    dt, code = (torch.float32, sv.SV_DTYPE_F32) if dtype == "f32" else (torch.bfloat16, sv.SV_DTYPE_BF16)
+    a, b = (sv.Cache(2, hq, hkv, d, code, mode, 1e4, sec, 1, 1400, 256) for _ in range(2))
+    g = torch.Generator(device="cuda:0").manual_seed(77)
+    rnd = lambda *shape: torch.randn(*shape, device="cuda:0", generator=g).to(dt)
+    run = gu.StreamRunner(b, *budgets)
+    pre = rnd(2, 2, 80, hkv, d)
+    for c in (a, b):
+        gu.StreamRunner(c, *budgets).preamble(list(pre[0]), list(pre[1]))
+    tol = gu.TOL[dtype]
+    for grid, t in (((1, 4, 4), 4), ((2, 3, 5), 1), ((1, 1, 7), 0), ((3, 2, 2), 64), ((1, 16, 16), 65), ((4, 1, 1), 3), ((1, 5, 3), 2)):
+        print(f"{dtype} d{d} mode {mode} {budgets} grid {grid} text {t}", flush=True)
+        n = grid[0] * grid[1] * grid[2]
+        thw = None if mode == sv.SV_ROPE_NONE and t == 1 else grid
+        q, k, v = rnd(2, n, hq, d), rnd(2, n, hkv, d), rnd(2, n, hkv, d)
+        qt, kt, vt = rnd(t, 2, 1, hq, d), rnd(t, 2, 1, hkv, d), rnd(t, 2, 1, hkv, d)
+        o, ot, o2, ot2 = torch.empty_like(q), torch.empty_like(qt), torch.empty_like(q), torch.empty_like(qt)
+        text = dict(q_text=qt, k_text=kt, v_text=vt, o_text=ot) if t else {}
+        kept = a.stream_step(0, *budgets, q_vision=q.clone(), k_vision=k, v_vision=v, o_vision=o, grid_thw=thw, **text)
+        assert kept == run.evict()
+        run.prefill(list(q.clone()), list(k), list(v), list(o2), thw)
+        for i in range(t):
+            run.decode(list(qt[i]), list(kt[i]), list(vt[i]), list(ot2[i]))
+        total = a.len(0)
+        assert total == b.len(0)
+        for x, y in zip(a.retained(0), b.retained(0)):
+            assert np.array_equal(x, y)
+        for layer in range(2):
+            for which in range(2):
+                assert np.array_equal(a.read_kv(0, layer, which, 0, total), b.read_kv(0, layer, which, 0, total)), (layer, which)
+        # (both are within the tolerance of the exact result, but for a rounding of the rotated queries)
+        assert gu.max_err(gu.host(o), gu.host(o2)) <= 2 * tol and (t == 0 or gu.max_err(gu.host(ot), gu.host(ot2)) <= 2 * tol)
+        m = t if t else n
+        x = rnd(m, hq, d)
+        y = x.clone()
+        a.rope_apply(0, total - m, m, x, None)
+        b.rope_apply(0, total - m, m, y, None)
+        assert torch.equal(x, y)
