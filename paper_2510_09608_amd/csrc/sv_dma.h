@@ -25,9 +25,30 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t lane_off, char*
                : "memory", "m0");
 }
 __device__ __forceinline__ uint32_t lds_addr(char* p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)p; }
-// ... with the base known to be uniform and the place in LDS as its address (lds_addr), which costs no scalar instructions per call
+// A pointer that is the same in all lanes, in scalar registers.
+__device__ __forceinline__ const char* uniform_ptr(const char* p) {
+  const uint64_t b = (uint64_t)p;
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b), hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+  return (const char*)((uint64_t)hi << 32 | lo);
+}
+// ... with the base known to be uniform and the place in LDS as its address (lds_addr), which costs no scalar instructions per
+// call.  NT: non-temporal.
+template <bool NT = false>
 __device__ __forceinline__ void dma16(const void* base, uint32_t lane_off, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(lane_off), "s"(base) : "memory", "m0");
+  if constexpr (NT)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(lane_off), "s"(base) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(lane_off), "s"(base) : "memory", "m0");
+}
+// Two of them, 1 KB further on in memory and in LDS (the instruction's offset counts for both).
+template <bool NT>
+__device__ __forceinline__ void dma16x2(const void* base, uint32_t lane_off, uint32_t lds) {
+  if constexpr (NT)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt\n\tglobal_load_lds_dwordx4 %1, %2 offset:1024 nt" ::"s"(
+                     lds), "v"(lane_off), "s"(base) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\tglobal_load_lds_dwordx4 %1, %2 offset:1024" ::"s"(
+                     lds), "v"(lane_off), "s"(base) : "memory", "m0");
 }
 #pragma clang diagnostic pop
 
