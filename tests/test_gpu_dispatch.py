@@ -591,3 +591,26 @@ def test_runs_registered_by_the_eviction(dtype, hq, hkv, d, mode, budgets):
         a.rope_apply(0, total - m, m, x, None)
         b.rope_apply(0, total - m, m, y, None)
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(4, 4, 128), (8, 8, 64)])
+@pytest.mark.parametrize("lens", [(33000, 32100, 1), (66000, 66100, 77), (70111, 31, 92161, 129)])
+def test_decode_batches_of_few_and_of_many_blocks_per_workgroup(hq, hkv, d, lens):
+    """Batches of more K and V than the caches hold, with runs of 8, of 16 and 17 and of 19 and 20 blocks per workgroup, against
+    float32.  The outputs of these lengths are small: the tolerance is the rounding of the result and six standard deviations of the
+    sum of the weights' roundings (2^-8 of a weight at most, independent of each other)."""
+    g = torch.Generator(device="cuda:0").manual_seed(91)
+    rnd = lambda *shape: torch.randn(*shape, device="cuda:0", generator=g).to(torch.bfloat16)
+    cache = sv.Cache(1, hq, hkv, d, sv.SV_DTYPE_BF16, sv.SV_ROPE_NONE, 1e4, (0, 0, 0), len(lens), max(lens) + 8, 1)
+    q, ref, tol = rnd(len(lens), hq, d), [], []
+    for b, n in enumerate(lens):
+        k, v = rnd(n, hkv, d), rnd(n, hkv, d)
+        for i in range(0, n, 16384):
+            cache.append(b, 0, np.zeros(min(16384, n - i), np.uint8), None, k[i:i + 16384].contiguous(), v[i:i + 16384].contiguous())
+        pv = torch.softmax((k.float() * q[b].float()).sum(2) / d ** 0.5, 0)[:, :, None] * v.float()
+        ref.append(pv.sum(0))
+        tol.append(2 ** -8 * ref[b].abs() + 6 * 2 ** -8 / 3 ** 0.5 * (pv * pv).sum(0).sqrt() + 1e-5)
+    out = torch.full_like(q, float("nan"))
+    cache.attn_decode(0, list(range(len(lens))), q, out)
+    err = (out.float() - torch.stack(ref)).abs()
+    assert bool((err <= torch.stack(tol)).all()), float((err / torch.stack(tol)).max())
