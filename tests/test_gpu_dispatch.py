@@ -614,3 +614,25 @@ def test_decode_batches_of_few_and_of_many_blocks_per_workgroup(hq, hkv, d, lens
     cache.attn_decode(0, list(range(len(lens))), q, out)
     err = (out.float() - torch.stack(ref)).abs()
     assert bool((err <= torch.stack(tol)).all()), float((err / torch.stack(tol)).max())
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(1, 1, 128), (3, 1, 128), (5, 1, 64), (12, 2, 128), (7, 1, 64), (8, 1, 128)])
+@pytest.mark.parametrize("n_q,n_kv", [(1, 200), (13, 205), (37, 300), (90, 400), (257, 1000)])
+def test_chunk_rows_of_every_group_size(hq, hkv, d, n_q, n_kv):
+    """The (token, head) rows of a wavefront, for groups that do and do not divide 32, chunks that end inside a wavefront's rows and a
+    workgroup's, as final results and as partial ones; queries and outputs at an offset of one element from 16 bytes."""
+    w = si.Workload("g", 1, hq, hkv, d, "bf16", 2, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, 9990)
+    q, k, v = w.qkv(0, np.arange(n_kv))
+    q = q[n_kv - n_q:]
+    cache = sv.Cache(1, hq, hkv, d, sv.SV_DTYPE_BF16, sv.SV_ROPE_NONE, 1e4, (0, 0, 0), 1, n_kv + 8, n_q)
+    cache.append(0, 0, np.zeros(n_kv, np.uint8), None, gu.dev(k, w), gu.dev(v, w))
+    ref = orc.gqa_attention(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), np.arange(n_kv - n_q, n_kv), True)
+    for splits in (1, 3):
+        for off in (0, 1):
+            buf = torch.full((2, q.size + 8), float("nan"), device="cuda:0", dtype=torch.bfloat16)
+            qd, od = (x[off:off + q.size].view(n_q, hq, d) for x in buf)
+            qd.copy_(gu.dev(q, w))
+            cache.set_option(sv.SV_OPT_CHUNK_SPLITS, splits)
+            cache.attn_chunk(0, 0, qd, od, True)
+            assert gu.max_err(gu.host(od), ref) <= gu.TOL["bf16"], (splits, off)
+            assert bool(torch.isnan(buf[1, :off]).all()) and bool(torch.isnan(buf[1, off + q.size:]).all())
