@@ -590,7 +590,9 @@ int sv_stream_step(sv_cache* c, int stream_id, int64_t n_sink, int64_t vision_wi
       rc = append_impl(c, stream_id, l, n, types.data(), has_grid ? io->grid_thw : nullptr, k, v, &slot0, hip_stream,
                        !fused, registered);
       if (rc != SV_OK) return rc;
-      if (fused && c->f32_mfma) {
+      if (fused && c->f32_mfma && sv::attn_chunk_f32_stores_tokens(c, stream_id, n)) {
+        SV_DEV(sv::launch_attn_chunk_f32(c, stream_id, l, q, n, o, 1, (hipStream_t)hip_stream, k, v));
+      } else if (fused && c->f32_mfma) {
         SV_DEV(sv::launch_store_tokens(c, stream_id, l, slot0, n, q, k, v, (hipStream_t)hip_stream));
         SV_DEV(sv::launch_attn_chunk_f32(c, stream_id, l, q, n, o, 1, (hipStream_t)hip_stream));
       } else if (fused) {

@@ -192,9 +192,11 @@ size_t decode_batch_bytes(const sv_config& cfg);    // bytes of sv_cache::part_b
 hipError_t launch_attn_decode_mfma_static(const sv_cache* c, int layer, const int32_t* streams, int n_list,
                                           const void* q, void* o, hipStream_t s);
 
-// Chunk prefill of fp32 caches (c->f32_mfma); q is rotated.
+// Chunk prefill of fp32 caches (c->f32_mfma); q is rotated.  k_new / v_new not NULL (only where attn_chunk_f32_stores_tokens): as
+// below, and q is un-rotated.
 hipError_t launch_attn_chunk_f32(const sv_cache* c, int stream, int layer, const void* q, int n_q, void* o, int causal,
-                                 hipStream_t s);
+                                 hipStream_t s, const void* k_new = nullptr, const void* v_new = nullptr);
+bool attn_chunk_f32_stores_tokens(const sv_cache* c, int stream, int n_q);
 
 // Once per process and device, before the first chunk-prefill launch: the kernel's LDS size has to be asked for.
 hipError_t attn_chunk_mfma_init();

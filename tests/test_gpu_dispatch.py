@@ -636,3 +636,30 @@ def test_chunk_rows_of_every_group_size(hq, hkv, d, n_q, n_kv):
             cache.attn_chunk(0, 0, qd, od, True)
             assert gu.max_err(gu.host(od), ref) <= gu.TOL["bf16"], (splits, off)
             assert bool(torch.isnan(buf[1, :off]).all()) and bool(torch.isnan(buf[1, off + q.size:]).all())
+
+
+@pytest.mark.parametrize("hq,hkv,d,mode", [(2, 1, 64, sv.SV_ROPE_1D), (3, 3, 64, sv.SV_ROPE_3D), (4, 2, 128, sv.SV_ROPE_3D), (5, 1, 128, sv.SV_ROPE_1D)])
+@pytest.mark.parametrize("n,kept", [(1, 1), (4, 28), (5, 28), (12, 20), (12, 21), (9, 90), (12, 116), (12, 117), (6, 122)])
+def test_f32_chunk_of_few_rows_that_stores_its_tokens(hq, hkv, d, mode, n, kept):
+    """A short fp32 chunk on up to 128 keys, one more, and where new keys begin inside a tile, whose attention launch (head_dim 64) rotates and
+    stores: the rows that a launch of its own would have stored, its outputs, and those of the oracle."""
+    sec = ((16, 24, 24) if d == 128 else (8, 12, 12)) if mode == sv.SV_ROPE_3D else (0, 0, 0)
+    a, b = (sv.Cache(1, hq, hkv, d, sv.SV_DTYPE_F32, mode, 1e4, sec, 1, 256, 64) for _ in range(2))
+    b.set_option(sv.SV_OPT_CHUNK_STORE, 1)
+    g = torch.Generator(device="cuda:0").manual_seed(78)
+    rnd = lambda *shape: torch.randn(*shape, device="cuda:0", generator=g)
+    pre, q, k, v = rnd(2, 1, kept, hkv, d), rnd(1, n, hq, d), rnd(1, n, hkv, d), rnd(1, n, hkv, d)
+    out = []
+    for c in (a, b):
+        gu.StreamRunner(c, 999, 999, 999).preamble(list(pre[0]), list(pre[1]))
+        o = torch.full_like(q, float("nan"))
+        c.stream_step(0, 999, 999, 999, q_vision=q.clone(), k_vision=k, v_vision=v, o_vision=o, grid_thw=(1, 1, n))
+        out.append(gu.host(o))
+    total = a.len(0)
+    assert total == kept + n == b.len(0)
+    rows = [[c.read_kv(0, 0, which, 0, total) for which in range(2)] for c in (a, b)]
+    assert all(np.array_equal(x, y) for x, y in zip(*rows))
+    x = q[0].clone()
+    a.rope_apply(0, kept, n, x, None)
+    ref = orc.gqa_attention(gu.host(x).astype(np.float64), rows[0][0].astype(np.float64), rows[0][1].astype(np.float64), np.arange(kept, total), True)
+    assert gu.max_err(out[0][0], ref) <= gu.TOL["f32"] and gu.max_err(out[1][0], ref) <= gu.TOL["f32"]
