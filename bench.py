@@ -31,8 +31,8 @@ MEASURED_TRAFFIC = {
     # attn_chunk = k_attn_chunk_pipe (which stores the chunk's K/V itself at this workload) + k_chunk_combine; decode_sweep =
     # k_decode_one (key ranges merged in the same launch); evict = k_evict_scan + k_compact (reads + writes, scaled counters)
     "qwen7b_256v_28L": {"attn_chunk": (29.5e6 + 18.1e6) + (18.0e6 + 1.8e6),
-                        "decode_sweep": 12.66e6 + 1.52e6,
-                        "evict": (264.5e6 + 264.2e6) + (0.4e6 + 0.3e6)},
+                        "decode_sweep": 12.69e6 + 1.52e6,
+                        "evict": (264.5e6 + 264.2e6) + (0.5e6 + 0.5e6)},
 }
 
 
@@ -236,7 +236,7 @@ def prefill_1024v_figure(Hq, Hkv, d, n_kv=18432, n_q=1024, layers=4, reps=40):
     """Extra figure, never `value`: chunk-prefill attention alone at the high-frame-rate shape (1024-token chunk over
     a 17.4k-token retained cache, the shape of --workload qwen7b_1024v_28L), where the MFMA kernel has its longest key
     ranges.  One `sv_attn_chunk` call per layer = attention + merge of the key ranges, timed with events on the
-    launch stream; the kernel-only duration is in profiles/kernel_trace_qwen7b_1024v_28L.txt."""
+    launch stream; the kernel-only duration is in profiles/kernel_times_by_workload.txt."""
     import numpy as np
     import torch
 

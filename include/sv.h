@@ -116,8 +116,9 @@ SV_API int sv_cache_destroy(sv_cache* c);
  *                                 leaves its share of the merge to those that are late, instead of after 4096 looks,
  *   SV_OPT_DECODE_SPLITS          the number of key ranges of the generic row kernel,
  *   SV_OPT_CHUNK_STORE            who stores a chunk's K/V in sv_stream_step on a matrix-core cache: 1 = always a
- *                                 launch of its own, 2 = the attention launch whenever it can (chunks of at most
- *                                 512 tokens with a rotary mode); 0 = whichever the library expects to be faster.
+ *                                 launch of its own, 2 = the attention launch whenever it can (bf16: chunks of at
+ *                                 most 512 tokens with a rotary mode; fp32: as 0); 0 = whichever the library
+ *                                 expects to be faster.
  * Forced values are still clamped to what the scratch buffers hold.  Host-side state only: takes effect
  * from the next launch.  Errors: SV_ERR_INVALID (NULL handle, unknown option, negative value).
  */
