@@ -663,3 +663,40 @@ def test_f32_chunk_of_few_rows_that_stores_its_tokens(hq, hkv, d, mode, n, kept)
     a.rope_apply(0, kept, n, x, None)
     ref = orc.gqa_attention(gu.host(x).astype(np.float64), rows[0][0].astype(np.float64), rows[0][1].astype(np.float64), np.arange(kept, total), True)
     assert gu.max_err(out[0][0], ref) <= gu.TOL["f32"] and gu.max_err(out[1][0], ref) <= gu.TOL["f32"]
+
+
+def layers_case(hq, hkv, d, n, layers, seed):
+    """A cache whose layers all hold the same n tokens: attention alone of the first and the last layer, then two fused steps through
+    all of them, whose tokens are the last of a key range or one of their own; every layer's result and row against the oracle."""
+    print(f"decode {hq}/{hkv} x {d} n={n} layers={layers}", flush=True)
+    w = si.Workload("y", 1, hq, hkv, d, "bf16", 2, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, seed)
+    cache = sv.Cache(layers, hq, hkv, d, sv.SV_DTYPE_BF16, sv.SV_ROPE_NONE, 1e4, (0, 0, 0), 1, n + 8, 1)
+    q, k, v = w.qkv(0, np.arange(n))
+    kd, vd = gu.dev(k, w), gu.dev(v, w)
+    for layer in range(layers):
+        cache.append(0, layer, np.zeros(n, np.uint8) if layer == 0 else None, None, kd, vd)
+    for i in range(3):
+        o = torch.full((layers, 1, hq, d), float("nan"), device="cuda:0", dtype=torch.bfloat16)
+        if i == 0:
+            qn, calls = q[n - 1:], (0, layers - 1)
+            for layer in calls:
+                cache.attn_decode(layer, [0], gu.dev(qn, w), o[layer])
+        else:
+            qn, kn, vn = w.qkv(0, np.arange(60000 + i, 60001 + i))
+            calls = range(layers)
+            for layer in calls:
+                cache.decode_step(layer, [0], gu.dev(qn, w), gu.dev(kn, w), gu.dev(vn, w), o[layer])
+            k, v = np.concatenate([k, kn]), np.concatenate([v, vn])
+        ref = orc.gqa_attention(qn.astype(np.float64), k.astype(np.float64), v.astype(np.float64), np.array([n + i - 1]), True)
+        for layer in calls:
+            assert gu.max_err(gu.host(o[layer]), ref) <= gu.TOL["bf16"], (i, layer)
+    for layer in (0, layers - 1):
+        assert np.array_equal(cache.read_kv(0, layer, 0, n - 2, 4), k[n - 2:]) and np.array_equal(cache.read_kv(0, layer, 1, n - 2, 4), v[n - 2:])
+
+
+@pytest.mark.parametrize("hq,hkv,d,n,layers", [
+    (12, 12, 128, 1108, 6), (12, 12, 128, 1110, 6), (12, 12, 128, 1227, 5), (12, 12, 128, 1229, 5), (12, 12, 128, 2686, 16),
+    (12, 12, 128, 2686, 17), (28, 4, 128, 3585, 5), (8, 8, 64, 3327, 6), (8, 8, 64, 3330, 6), (1, 1, 128, 13313, 6)])
+def test_decode_k_tiles_through_lds_and_into_registers(hq, hkv, d, n, layers):
+    """One tile per wavefront, on both sides of what sends K through LDS: 6.5 MB in the launch, 36 MB in all layers, and 256 MB."""
+    layers_case(hq, hkv, d, n, layers, 9995)
