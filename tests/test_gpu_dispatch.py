@@ -700,3 +700,11 @@ def layers_case(hq, hkv, d, n, layers, seed):
 def test_decode_k_tiles_through_lds_and_into_registers(hq, hkv, d, n, layers):
     """One tile per wavefront, on both sides of what sends K through LDS: 6.5 MB in the launch, 36 MB in all layers, and 256 MB."""
     layers_case(hq, hkv, d, n, layers, 9995)
+
+
+@pytest.mark.parametrize("hq,hkv,d,n,layers", [
+    (12, 12, 128, 2688, 17), (12, 12, 128, 2689, 17), (12, 12, 128, 3041, 15), (12, 12, 128, 3700, 11), (12, 12, 128, 3700, 12),
+    (12, 12, 128, 4300, 11), (12, 12, 128, 4865, 9), (28, 4, 128, 8225, 15), (28, 4, 128, 8225, 16)])
+def test_decode_key_ranges_of_layers_within_the_infinity_cache_and_beyond(hq, hkv, d, n, layers):
+    """More key ranges of 128 keys than CUs: ranges of 256 keys up to 256 MB in all layers, of 160, 192, 224 and 256 beyond."""
+    layers_case(hq, hkv, d, n, layers, 9996)
