@@ -708,3 +708,33 @@ def test_decode_k_tiles_through_lds_and_into_registers(hq, hkv, d, n, layers):
 def test_decode_key_ranges_of_layers_within_the_infinity_cache_and_beyond(hq, hkv, d, n, layers):
     """More key ranges of 128 keys than CUs: ranges of 256 keys up to 256 MB in all layers, of 160, 192, 224 and 256 beyond."""
     layers_case(hq, hkv, d, n, layers, 9996)
+
+
+@pytest.mark.parametrize("lens", [(131072, 98000, 31), (131072, 102400, 31)])
+def test_decode_batches_on_both_sides_of_56_blocks_per_workgroup(lens):
+    """Runs of 56 blocks, whose K goes through LDS, and of 57, whose does not (non-temporal loads)."""
+    test_decode_batches_of_few_and_of_many_blocks_per_workgroup(8, 8, 64, lens)
+
+
+@pytest.mark.parametrize("n", [28600, 29200])
+def test_layers_as_rows_on_both_sides_of_56_blocks_per_workgroup(n):
+    """The same with plain loads: 64 layers of one stream in one launch, after a fused step and one more, whose token the first one
+    stored; tolerance as for the batches."""
+    layers, d = 64, 64
+    g = torch.Generator(device="cuda:0").manual_seed(92)
+    rnd = lambda *shape: torch.randn(*shape, device="cuda:0", generator=g).to(torch.bfloat16)
+    cache = sv.Cache(layers, 1, 1, d, sv.SV_DTYPE_BF16, sv.SV_ROPE_NONE, 1e4, (0, 0, 0), 1, n + 8, 1)
+    k, v = rnd(n, 1, d), rnd(n, 1, d)
+    for layer in range(layers):
+        cache.append(0, layer, np.zeros(n, np.uint8) if layer == 0 else None, None, k, v)
+    k, v = (x.expand(layers, n, d) for x in (k[:, 0], v[:, 0]))
+    for step in range(2):
+        q, kn, vn = rnd(layers, 1, d), rnd(layers, 1, d), rnd(layers, 1, d)
+        out = torch.full_like(q, float("nan"))
+        cache.decode_step_layers(0, q, kn, vn, out)
+        k, v = torch.cat([k, kn], 1), torch.cat([v, vn], 1)
+        pv = torch.softmax((k.float() * q.float()).sum(2) / d ** 0.5, 1)[:, :, None] * v.float()
+        ref = pv.sum(1)
+        tol = 2 ** -8 * ref.abs() + 6 * 2 ** -8 / 3 ** 0.5 * (pv * pv).sum(1).sqrt() + 1e-5
+        err = (out[:, 0].float() - ref).abs()
+        assert bool((err <= tol).all()), (step, float((err / tol).max()))
