@@ -176,7 +176,8 @@ __global__ __launch_bounds__(64) void k_meta_tokens(MetaPtrs m0, MetaPtrs m1, in
 // Registration.  A second's eviction is followed by the registration of its vision and of its text tokens, which needs nothing
 // from it but the position counter.  Where the caller knows them (sv_stream_step), `n_reg` more workgroups without tokens of their
 // own, behind the others, wait for the totals as those do and write what k_meta_append would have, in two launches (the smallest
-// second, fp32, 1 layer, 16 + 4 tokens, where every launch is 3 to 4 us of the host: 42.9 -> 38.9 us).
+// second, fp32, 1 layer, 16 + 4 tokens, where every launch is 3 to 4 us of the host: 42.9 -> 38.9 us).  An instantiation of its own
+// (R: one Registration, or nothing): in a plain eviction's it cost 34 spilled SGPRs.
 // ---------------------------------------------------------------------------------
 constexpr int kScanThreads = 256;
 constexpr int kScanWaves = kScanThreads / 64;
@@ -199,22 +200,30 @@ __device__ __forceinline__ int wave_scan(int x) {
   return x;
 }
 
+struct Registration {
+  int n_reg;
+  NewRuns runs;
+  int rope3d, s0, s01;
+  float2 *cs_tab, *last_cs;
+};
+
+template <typename... R>
 __global__ __launch_bounds__(kScanThreads) void k_evict_scan(MetaPtrs in, MetaPtrs out, int32_t* __restrict__ src,
                                                              int32_t* __restrict__ turn, float2* __restrict__ dtab,
                                                              const double* __restrict__ inv_freq, int half,
                                                              int f32_data, int32_t* __restrict__ next_out,
                                                              int32_t* __restrict__ n_out, int n_old, int64_t n_sink,
                                                              int64_t text_lo, int64_t vis_lo, int passes,
-                                                             unsigned long long* agg, int n_reg, NewRuns runs, int rope3d, int s0,
-                                                             int s01, float2* __restrict__ cs_tab,
-                                                             float2* __restrict__ last_cs) {
+                                                             unsigned long long* agg, R... reg) {
+  constexpr bool REG = sizeof...(R) > 0;
   __shared__ int2 sh_pass[kScanWaves], sh_all[kScanWaves], sh_carry[kScanWaves];   // {kept tokens, advance}
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int w = blockIdx.x, span = passes * kScanThreads;
   const int first = w * span;
   const uint32_t tag_old = (uint32_t)agg[2 * kScanWords];   // written by the launch before this one
   const double my_freq = dtab != nullptr && lane < half ? inv_freq[lane] : 0.0;
-  const bool registers = w >= (int)gridDim.x - n_reg;
+  bool registers = false;
+  if constexpr (REG) registers = w >= (int)gridDim.x - (reg, ...).n_reg;
 
   // The token and its successor (the look-ahead for "last of its block").  Indices are clamped instead of guarded
   // and the rule below is written without short-circuits, so that every load is unconditional and all nine go out
@@ -379,38 +388,44 @@ __global__ __launch_bounds__(kScanThreads) void k_evict_scan(MetaPtrs in, MetaPt
     }
     if (keep) turn[d] = row;
   }
-  // ---- registration: the scalar position counter is the sum of all advances
-  const int adv_vis = rope3d && runs.blk >= 0 ? max(runs.gT, max(runs.gH, runs.gW)) : runs.n_vision;
-  if (registers) {
-    const int n_new = runs.n_vision + runs.n_text, next_text = run_adv + adv_vis;
-    const int64_t slot_text = (int64_t)runs.n_kept + runs.n_vision;
-    const int at = (w - ((int)gridDim.x - n_reg)) * kScanThreads + tid, step = n_reg * kScanThreads;
-    auto cs_of = [&](int j, int i) {
-      const bool vis = j < runs.n_vision;
-      const int p = vis ? angle_pos(runs.n_kept, j, i, run_adv, rope3d, runs.blk, runs.gH, runs.gW, s0, s01)
-                        : angle_pos(slot_text, j - runs.n_vision, i, next_text, rope3d, -1, 1, 1, s0, s01);
-      return angle_cs(p, inv_freq[i], f32_data);
-    };
-    for (int j = at; j < n_new; j += step) {
-      if (j < runs.n_vision)
-        write_token(out, runs.n_kept, j, run_adv, SV_VISION, runs.gid0 + j, runs.rank_vis0 + j, rope3d, runs.blk, runs.gT, runs.gH, runs.gW);
-      else
-        write_token(out, slot_text, j - runs.n_vision, next_text, SV_TEXT, runs.gid0 + j, runs.rank_text0 + (j - runs.n_vision), rope3d,
-                    -1, 1, 1, 1);
-    }
-    if (dtab != nullptr)
-      for (int x = at; x < n_new * half; x += step) {
-        const float2 cs = cs_of(x / half, x % half);
-        cs_tab[x] = cs;
-        if (x / half == n_new - 1) last_cs[x % half] = cs;
+  int new_cnt = 0, new_adv = 0;   // registered tokens, and what they move the scalar position counter by
+  if constexpr (REG) {
+    const Registration& g = (reg, ...);
+    const NewRuns& runs = g.runs;
+    const int adv_vis = g.rope3d && runs.blk >= 0 ? max(runs.gT, max(runs.gH, runs.gW)) : runs.n_vision;
+    new_cnt = runs.n_vision + runs.n_text, new_adv = adv_vis + runs.n_text;
+    if (registers) {   // the position counter is the sum of all advances
+      const int next_text = run_adv + adv_vis;
+      const int64_t slot_text = (int64_t)runs.n_kept + runs.n_vision;
+      const int at = (w - ((int)gridDim.x - g.n_reg)) * kScanThreads + tid, step = g.n_reg * kScanThreads;
+      auto cs_of = [&](int j, int i) {
+        const bool vis = j < runs.n_vision;
+        const int p = vis ? angle_pos(runs.n_kept, j, i, run_adv, g.rope3d, runs.blk, runs.gH, runs.gW, g.s0, g.s01)
+                          : angle_pos(slot_text, j - runs.n_vision, i, next_text, g.rope3d, -1, 1, 1, g.s0, g.s01);
+        return angle_cs(p, inv_freq[i], f32_data);
+      };
+      for (int j = at; j < new_cnt; j += step) {
+        if (j < runs.n_vision)
+          write_token(out, runs.n_kept, j, run_adv, SV_VISION, runs.gid0 + j, runs.rank_vis0 + j, g.rope3d, runs.blk, runs.gT, runs.gH,
+                      runs.gW);
+        else
+          write_token(out, slot_text, j - runs.n_vision, next_text, SV_TEXT, runs.gid0 + j, runs.rank_text0 + (j - runs.n_vision),
+                      g.rope3d, -1, 1, 1, 1);
       }
-    else if (at < half)
-      last_cs[at] = make_float2(1.f, 0.f);
+      if (dtab != nullptr)
+        for (int x = at; x < new_cnt * half; x += step) {
+          const float2 cs = cs_of(x / half, x % half);
+          g.cs_tab[x] = cs;
+          if (x / half == new_cnt - 1) g.last_cs[x % half] = cs;
+        }
+      else if (at < half)
+        g.last_cs[at] = make_float2(1.f, 0.f);
+    }
   }
   if (w == (int)gridDim.x - 1) {
     if (tid == 0) {
-      *next_out = n_reg > 0 ? run_adv + adv_vis + runs.n_text : run_adv;
-      *n_out = n_reg > 0 ? run_cnt + runs.n_vision + runs.n_text : run_cnt;
+      *next_out = run_adv + new_adv;
+      *n_out = run_cnt + new_cnt;
       agg[2 * kScanWords] = tag;
     }
     for (int b = (int)gridDim.x + tid; b < kScanWords; b += kScanThreads) agg[2 * b] = 0ull, agg[2 * b + 1] = 0ull;
@@ -473,12 +488,19 @@ hipError_t launch_evict_scan(const sv_cache* c, int stream, int next_parity, int
   const int passes = (tiles + kScanMaxWG - 1) / kScanMaxWG;
   const int wgs = (tiles + passes - 1) / passes;
   unsigned long long* agg = c->scan_agg + (size_t)stream * 2 * (kScanWords + 1);
-  hipLaunchKernelGGL(k_evict_scan, dim3(wgs + n_reg), dim3(kScanThreads), 0, s, in, out, c->src + off, c->turn + off,
-                     c->cfg.rope_mode != SV_ROPE_NONE ? c->dtab + off * half : nullptr, c->inv_freq, half,
-                     c->cfg.dtype == SV_DTYPE_F32 ? 1 : 0, c->next_pos + 2 * stream + (next_parity ^ 1), c->n_dev + stream, (int)n_old, n_sink, text_lo,
-                     vis_lo, passes, agg, n_reg, runs ? *runs : NewRuns{}, c->cfg.rope_mode == SV_ROPE_3D ? 1 : 0, c->cfg.mrope_sections[0],
-                     c->cfg.mrope_sections[0] + c->cfg.mrope_sections[1], c->cs_tab + (size_t)stream * c->cs_rows * half,
-                     c->last_cs + (size_t)stream * half);
+  auto launch = [&](auto kernel, auto... reg) {
+    hipLaunchKernelGGL(kernel, dim3(wgs + n_reg), dim3(kScanThreads), 0, s, in, out, c->src + off, c->turn + off,
+                       c->cfg.rope_mode != SV_ROPE_NONE ? c->dtab + off * half : nullptr, c->inv_freq, half,
+                       c->cfg.dtype == SV_DTYPE_F32 ? 1 : 0, c->next_pos + 2 * stream + (next_parity ^ 1), c->n_dev + stream, (int)n_old,
+                       n_sink, text_lo, vis_lo, passes, agg, reg...);
+  };
+  if (runs)
+    launch(k_evict_scan<Registration>,
+           Registration{n_reg, *runs, c->cfg.rope_mode == SV_ROPE_3D ? 1 : 0, c->cfg.mrope_sections[0],
+                        c->cfg.mrope_sections[0] + c->cfg.mrope_sections[1], c->cs_tab + (size_t)stream * c->cs_rows * half,
+                        c->last_cs + (size_t)stream * half});
+  else
+    launch(k_evict_scan<>);
   return hipGetLastError();
 }
 

@@ -738,3 +738,40 @@ def test_layers_as_rows_on_both_sides_of_56_blocks_per_workgroup(n):
         tol = 2 ** -8 * ref.abs() + 6 * 2 ** -8 / 3 ** 0.5 * (pv * pv).sum(1).sqrt() + 1e-5
         err = (out[:, 0].float() - ref).abs()
         assert bool((err <= tol).all()), (step, float((err / tol).max()))
+
+
+@pytest.mark.parametrize("total", [30000, 40000, 70000])
+def test_runs_registered_by_scans_of_several_passes(total):
+    """Seconds behind evictions whose scan has up to 128 workgroups of tokens, one or several passes each, and as many registering ones
+    as there can be (their words lie behind the others'), then behind shorter ones, which clear what they do not use: retained ids and
+    positions as the oracle has them, the second's stored K as rotated at those positions, V as given."""
+    print(f"long-cache second: {total} tokens", flush=True)
+    d, sec, grid, nv, nt = 64, (8, 12, 12), (2, 24, 30), 1440, 37
+    cache = sv.Cache(1, 1, 1, d, sv.SV_DTYPE_F32, sv.SV_ROPE_3D, 1e4, sec, 1, total + 4096, 2048)
+    o = orc.OracleStream(1, 1, 1, 2, orc.ROPE_3D, 1e4, (1, 0, 0))
+    z, zt = (lambda n: np.zeros((n, 1, 2))), torch.zeros(1024, 1, d, device="cuda:0")
+    g = torch.Generator(device="cuda:0").manual_seed(79)
+    rnd = lambda *shape: torch.randn(*shape, device="cuda:0", generator=g)
+    n = 0
+    while n < total:
+        for ty, cnt, thw in ((orc.VISION, 2 * 12 * 16, (2, 12, 16)), (orc.TEXT, 37, None)):
+            cache.append(0, 0, np.full(cnt, 1 if ty == orc.VISION else 0, dtype=np.uint8), thw, zt[:cnt], zt[:cnt])
+            o.append_meta([ty] * cnt, thw)
+            o.append_kv(0, z(cnt), z(cnt))
+            n += cnt
+    for budgets in [(100, total - 6000, total // 20), (64, total // 3, 333), (64, 3000, 333), (0, 100, 0), (64, 5000, 333)]:
+        k, v, kt, vt = rnd(1, nv, 1, d), rnd(1, nv, 1, d), rnd(nt, 1, 1, 1, d), rnd(nt, 1, 1, 1, d)
+        q, qt = rnd(1, nv, 1, d), rnd(nt, 1, 1, 1, d)
+        kept = cache.stream_step(0, *budgets, q_vision=q, k_vision=k, v_vision=v, o_vision=torch.empty_like(q), grid_thw=grid,
+                                 q_text=qt, k_text=kt, v_text=vt, o_text=torch.empty_like(qt))
+        assert kept == o.evict(*budgets)
+        for ty, cnt, thw in ((orc.VISION, nv, grid), (orc.TEXT, nt, None)):
+            o.append_meta([ty] * cnt, thw)
+            o.append_kv(0, z(cnt), z(cnt))
+        ids, pos = cache.retained(0)
+        assert np.array_equal(ids, np.asarray(o.gid, dtype=np.int64))
+        assert np.array_equal(pos.astype(np.int64), o.positions())
+        kn = np.concatenate([gu.host(k)[0], gu.host(kt)[:, 0, 0]])
+        vn = np.concatenate([gu.host(v)[0], gu.host(vt)[:, 0, 0]])
+        assert gu.max_err(cache.read_kv(0, 0, 0, kept, nv + nt), orc.rope(kn, o.positions()[kept:], orc.ROPE_3D, 1e4, sec)) <= gu.TOL["f32"]
+        assert np.array_equal(cache.read_kv(0, 0, 1, kept, nv + nt), vn.astype(np.float32))
