@@ -528,8 +528,9 @@ def test_decode_outputs_shared_out_in_finer_units(dtype, hq, hkv, d, n):
     (12, 12, 128, 2688), (12, 12, 128, 2689), (12, 12, 128, 3040), (12, 12, 128, 3041), (12, 12, 128, 3700), (12, 12, 128, 4300),
     (12, 12, 128, 4865), (16, 4, 64, 8225), (8, 1, 128, 8193), (8, 1, 128, 10300)])
 def test_decode_key_ranges_between_one_tile_per_wavefront_and_two(hq, hkv, d, n):
-    """Lengths at which a single stream's ranges become 160, 192, 224 and 256 keys long and where that ends: attention alone, then
-    two fused steps, whose token is the last of a range, or one of its own."""
+    """Lengths at which a single stream's ranges become 160, 192, 224 and 256 keys long and where that ends (with more than 256 MB in all
+    layers, see test_decode_key_ranges_of_layers_within_the_infinity_cache_and_beyond; a single layer, as here, has ranges of 256 keys
+    at those of more than one kv head): attention alone, then two fused steps, whose token is the last of a range, or one of its own."""
     cache, w, q, k, v = attn_case("bf16", hq, hkv, d, n, 1, True, 9980)
     new = [w.qkv(0, np.arange(60000 + i, 60001 + i)) for i in range(2)]
     for i in range(3):
