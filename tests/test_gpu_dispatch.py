@@ -776,3 +776,31 @@ def test_runs_registered_by_scans_of_several_passes(total):
         vn = np.concatenate([gu.host(v)[0], gu.host(vt)[:, 0, 0]])
         assert gu.max_err(cache.read_kv(0, 0, 0, kept, nv + nt), orc.rope(kn, o.positions()[kept:], orc.ROPE_3D, 1e4, sec)) <= gu.TOL["f32"]
         assert np.array_equal(cache.read_kv(0, 0, 1, kept, nv + nt), vn.astype(np.float32))
+
+
+@pytest.mark.parametrize("hq,hkv,d,lens,layers", [
+    (12, 12, 128, (1280, 1270), 6), (12, 12, 128, (1280, 1270), 2), (28, 4, 128, (2048, 1983, 2040), 5), (8, 8, 64, (2046, 2000), 5)])
+def test_decode_batches_of_one_block_per_workgroup(hq, hkv, d, lens, layers):
+    """Batches of one key block per workgroup, K into registers where the layers together are 36 to 256 MB: attention alone, then two
+    fused steps through all layers, the second of which reads what the first one stored."""
+    w = si.Workload("o", 1, hq, hkv, d, "bf16", 2, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, 9997)
+    cache = sv.Cache(layers, hq, hkv, d, sv.SV_DTYPE_BF16, sv.SV_ROPE_NONE, 1e4, (0, 0, 0), len(lens), max(lens) + 8, 1)
+    ids, kv = list(range(len(lens))), []
+    for b, n in enumerate(lens):
+        _, k, v = w.qkv(b, np.arange(n))
+        kv.append((k, v))
+        for layer in range(layers):
+            cache.append(b, layer, np.zeros(n, np.uint8) if layer == 0 else None, None, gu.dev(k, w), gu.dev(v, w))
+    for i in range(3):
+        q, kn, vn = w.qkv(0, np.arange(60000 + 10 * i, 60000 + 10 * i + len(lens)))
+        o = torch.full((layers, len(lens), hq, d), float("nan"), device="cuda:0", dtype=torch.bfloat16)
+        for layer in range(layers):
+            if i == 0:
+                cache.attn_decode(layer, ids, gu.dev(q, w), o[layer])
+            else:
+                cache.decode_step(layer, ids, gu.dev(q, w), gu.dev(kn, w), gu.dev(vn, w), o[layer])
+        if i > 0:
+            kv = [(np.concatenate([k, kn[b:b + 1]]), np.concatenate([v, vn[b:b + 1]])) for b, (k, v) in enumerate(kv)]
+        ref = batch_ref(q, kv, [len(k) for k, _ in kv], hq // hkv)
+        for layer in range(layers):
+            assert gu.max_err(gu.host(o[layer]), ref) <= gu.TOL["bf16"], (i, layer)
