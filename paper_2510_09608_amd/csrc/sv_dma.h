@@ -1,4 +1,4 @@
-// Direct global -> LDS loads, shared by the chunk-prefill kernels.
+// Direct global -> LDS loads, shared by the attention kernels.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -9,7 +9,7 @@ namespace sv {
 // 16 bytes per lane from global memory straight into LDS: lane L's bytes land at lds_dst + 16 L (lds_dst is
 // uniform over the wavefront and travels in M0).  Written as assembly on purpose: the compiler then does not
 // see a pending write to LDS and inserts no wait for ALL outstanding direct loads in front of later LDS
-// reads; the kernel waits itself (vmcnt(0), then a workgroup barrier) before a tile is first read.
+// reads; the kernel waits itself (vmcnt, and a workgroup barrier where other wavefronts read it) before a tile is first read.
 // (M0 is named as clobbered on purpose: nothing else in these kernels uses it, and the compiler must not assume it
 // survives; clang notes that M0 is a reserved register, which is the point.)
 #pragma clang diagnostic push

@@ -804,3 +804,38 @@ def test_decode_batches_of_one_block_per_workgroup(hq, hkv, d, lens, layers):
         ref = batch_ref(q, kv, [len(k) for k, _ in kv], hq // hkv)
         for layer in range(layers):
             assert gu.max_err(gu.host(o[layer]), ref) <= gu.TOL["bf16"], (i, layer)
+
+
+@pytest.mark.parametrize("hq,hkv,d,lens", [(12, 12, 128, (1500,)), (28, 4, 128, (3650,)), (8, 8, 64, (3400,)), (12, 12, 128, (1280, 1265))])
+@pytest.mark.parametrize("mode", [sv.SV_ROPE_1D, sv.SV_ROPE_3D])
+def test_decode_is_bit_for_bit_the_same_however_k_travels(hq, hkv, d, lens, mode):
+    """The same tokens in a cache of one layer, whose K goes through LDS, and in one of six, whose K goes into registers: fused steps with
+    rotation, attention alone and with static scratch, and what the steps stored."""
+    sec = ((16, 24, 24) if d == 128 else (8, 12, 12)) if mode == sv.SV_ROPE_3D else (0, 0, 0)
+    caches = [sv.Cache(layers, hq, hkv, d, sv.SV_DTYPE_BF16, mode, 1e4, sec, len(lens), max(lens) + 8, 16) for layers in (1, 6)]
+    g = torch.Generator(device="cuda:0").manual_seed(93)
+    rnd = lambda *shape: torch.randn(*shape, device="cuda:0", generator=g).to(torch.bfloat16)
+    ids = list(range(len(lens)))
+    for b, n in enumerate(lens):
+        k, v = rnd(n, hkv, d), rnd(n, hkv, d)
+        for c in caches:
+            for layer in range(c.cfg.n_layers):
+                c.append(b, layer, np.zeros(n, np.uint8) if layer == 0 else None, None, k, v)
+    for step in range(3):
+        print(f"decode {hq}/{hkv} x {d} {lens} mode {mode} step {step}", flush=True)
+        q, kn, vn = rnd(len(lens), hq, d), rnd(len(lens), hkv, d), rnd(len(lens), hkv, d)
+        out = []
+        for c in caches:
+            for layer in range(c.cfg.n_layers):
+                o = torch.full((3, len(lens), hq, d), float("nan"), device="cuda:0", dtype=torch.bfloat16)
+                c.attn_decode(layer, ids, q, o[0])
+                c.attn_decode_static(layer, ids, q, o[1])
+                out.append(o)
+            for layer in range(c.cfg.n_layers):
+                c.decode_step(layer, ids, q, kn, vn, out[layer - c.cfg.n_layers][2])
+        assert not torch.isnan(out[0]).any() and torch.equal(out[0][0], out[0][1])
+        assert all(torch.equal(out[0], o) for o in out[1:])
+    for b, n in enumerate(lens):
+        for which in range(2):
+            rows = [c.read_kv(b, layer, which, n - 4, 7) for c in caches for layer in (0, c.cfg.n_layers - 1)]
+            assert all(np.array_equal(rows[0], x) for x in rows[1:])
