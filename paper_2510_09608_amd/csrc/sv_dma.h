@@ -1,4 +1,4 @@
-// Direct global -> LDS loads, shared by the attention kernels.
+// Direct global -> LDS loads and stores past the L2, shared by the attention kernels.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -51,5 +51,31 @@ __device__ __forceinline__ void dma16x2(const void* base, uint32_t lane_off, uin
                      lds), "v"(lane_off), "s"(base) : "memory", "m0");
 }
 #pragma clang diagnostic pop
+
+// A store that goes through the L2 to memory (device scope) instead of waiting there as a dirty line.  A launch ends with the
+// write-back of the eight L2s: of what its last workgroups stored, at least, nothing has left by itself, and the next launch
+// starts that much later; and a launch with no dirty line at all ends sooner than one with a few.  So it counts for launches of
+// microseconds that write to their end, and there only if ALL their stores are of this kind.
+// Chunk attention with its merge, 256 queries of 28 / 4 heads, on 1376 keys 21.1 -> 19.9 us, on 5376 30.7 -> 29.7 (its last
+// partial result was stored after 25.4 us, the merge began after 28.4); decode, 28 / 4 heads, 5392 tokens, 6.10 -> 6.00.
+// Not used where it gains nothing: the moves of whole caches (76 us at head_dim 128 either way; 12 layers of 64 11.6 and 17), the
+// storing of new tokens, fp32 chunk attention (256 on 5392, 4 layers and their decode, 788 us, with it 793).
+// (16 bytes as assembly, which has no builtin; the s_nop keeps the compiler, which does not know of the store, from
+// overwriting its registers in the very next instruction.)
+template <typename V>
+__device__ __forceinline__ void store_through(void* p, const V& v) {
+  static_assert(sizeof(V) == 2 || sizeof(V) == 4 || sizeof(V) == 8 || sizeof(V) == 16, "one store");
+  if constexpr (sizeof(V) == 16) {
+    typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
+    const u32x4 x = __builtin_bit_cast(u32x4, v);
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(x) : "memory");
+  } else if constexpr (sizeof(V) == 8) {
+    __hip_atomic_store((unsigned long long*)p, __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else if constexpr (sizeof(V) == 4) {
+    __hip_atomic_store((uint32_t*)p, __builtin_bit_cast(uint32_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else {
+    __hip_atomic_store((unsigned short*)p, __builtin_bit_cast(unsigned short, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
 
 }  // namespace sv
