@@ -839,3 +839,29 @@ def test_decode_is_bit_for_bit_the_same_however_k_travels(hq, hkv, d, lens, mode
         for which in range(2):
             rows = [c.read_kv(b, layer, which, n - 4, 7) for c in caches for layer in (0, c.cfg.n_layers - 1)]
             assert all(np.array_equal(rows[0], x) for x in rows[1:])
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d,step", [
+    ("bf16", 28, 4, 128, 128), ("bf16", 16, 2, 64, 128), ("bf16", 3, 3, 128, 128), ("f32", 8, 2, 128, 64), ("f32", 2, 1, 64, 64)])
+def test_decode_ranges_whose_wavefronts_have_one_tile_or_none(dtype, hq, hkv, d, step):
+    """One to four key ranges of one tile per wavefront, the last of them with one to four tiles, whole or a key more or less: attention
+    alone and a fused step, whose token is in the last tile or is a tile of its own."""
+    lens = [step * n + m for n in range(4) for m in (1, step // 4 - 1, step // 4, step // 4 + 1, step // 2, step - 1)] + [4 * step]
+    w = si.Workload("o", 1, hq, hkv, d, dtype, 2, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, 9997)
+    cache = sv.Cache(1, hq, hkv, d, sv.SV_DTYPE_F32 if dtype == "f32" else sv.SV_DTYPE_BF16, sv.SV_ROPE_NONE, 1e4, (0, 0, 0),
+                     len(lens), max(lens) + 8, 16)
+    q, k, v = w.qkv(0, np.arange(max(lens) + 1))
+    f64 = lambda x: x.astype(np.float64)
+    for b, n in enumerate(lens):
+        cache.append(b, 0, np.zeros(n, np.uint8), None, gu.dev(k[:n], w), gu.dev(v[:n], w))
+        for new in (False, True):
+            m = n + new
+            print(f"{dtype} {hq}/{hkv} x {d} n={n} new={new}", flush=True)
+            od = torch.full((1, hq, d), float("nan"), device="cuda:0", dtype=gu.tdtype(w))
+            if new:
+                cache.decode_step(0, [b], gu.dev(q[n:m], w), gu.dev(k[n:m], w), gu.dev(v[n:m], w), od)
+            else:
+                cache.attn_decode(0, [b], gu.dev(q[n - 1:n], w), od)
+            ref = orc.gqa_attention(f64(q[m - 1:m]), f64(k[:m]), f64(v[:m]), np.array([m - 1]), True)
+            assert gu.max_err(gu.host(od), ref) <= gu.TOL[dtype]
+        assert np.array_equal(cache.read_kv(b, 0, 0, n, 1), k[n:n + 1]) and np.array_equal(cache.read_kv(b, 0, 1, n, 1), v[n:n + 1])
