@@ -60,15 +60,15 @@ __device__ __forceinline__ void dma16x2(const void* base, uint32_t lane_off, uin
 // partial result was stored after 25.4 us, the merge began after 28.4); decode, 28 / 4 heads, 5392 tokens, 6.10 -> 6.00.
 // Not used where it gains nothing: the moves of whole caches (76 us at head_dim 128 either way; 12 layers of 64 11.6 and 17), the
 // storing of new tokens, fp32 chunk attention (256 on 5392, 4 layers and their decode, 788 us, with it 793).
-// (16 bytes as assembly, which has no builtin; the s_nop keeps the compiler, which does not know of the store, from
-// overwriting its registers in the very next instruction.)
+// (16 bytes as assembly, which has no builtin; the s_nop keeps the compiler, which does not know of the store, from overwriting its
+// registers while they are read: a vector instruction that does so has to stay two wait states behind a store of more than 8 bytes.)
 template <typename V>
 __device__ __forceinline__ void store_through(void* p, const V& v) {
   static_assert(sizeof(V) == 2 || sizeof(V) == 4 || sizeof(V) == 8 || sizeof(V) == 16, "one store");
   if constexpr (sizeof(V) == 16) {
     typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
     const u32x4 x = __builtin_bit_cast(u32x4, v);
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(x) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(x) : "memory");
   } else if constexpr (sizeof(V) == 8) {
     __hip_atomic_store((unsigned long long*)p, __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   } else if constexpr (sizeof(V) == 4) {
