@@ -86,7 +86,7 @@ Layout make_layout(const sv_config& c) {
   L.next_pos = take(S * 2 * 4);
   L.n_dev = take(S * 4);
   L.inv_freq = take((size_t)(c.head_dim / 2) * 8);
-  L.last_cs = take(S * (size_t)(c.head_dim / 2) * 8);
+  L.last_cs = take(S * (size_t)sv::kAhead * (size_t)(c.head_dim / 2) * 8);
   L.cs_tab = take(S * ((size_t)c.max_q_tokens + sv::kTextRows) * (size_t)(c.head_dim / 2) * 8);
   L.part_rows = std::max<int64_t>(64 * (int64_t)c.n_streams, std::max<int64_t>(4096, 4 * (int64_t)c.max_q_tokens));
   L.part_o = take((size_t)L.part_rows * c.n_q_heads * c.head_dim * 4);
@@ -128,19 +128,60 @@ std::vector<std::pair<int64_t, int64_t>> iv_after_evict(
   return out;
 }
 
-// Host bookkeeping of n text tokens registered at the end of a stream (the metadata launch is the caller's).  with_vision: by the
-// launch that registered the vision run in front of them.
-void note_text_registered(sv::StreamState& st, int n, bool cs_tab_valid, bool with_vision = false) {
-  st.cs_row0 = with_vision ? st.pending_n : 0;
+// Host bookkeeping of n text tokens registered at the end of a stream (the metadata launch is the caller's).  turned: that launch
+// has moved the position counter (not by the launch that registered the vision run in front of them, nor by one of an earlier
+// decode step).
+void note_text(sv::StreamState& st, int n, bool cs_tab_valid, bool turned) {
   st.cs_tab_valid = cs_tab_valid;
   st.pending_slot0 = st.len;
   st.pending_n = n;
-  if (!with_vision) st.next_parity ^= 1;
+  if (turned) st.next_parity ^= 1;
   st.next_gid += n;
   if (!st.text_iv.empty() && st.text_iv.back().second == st.n_text) st.text_iv.back().second += n;
   else st.text_iv.emplace_back(st.n_text, st.n_text + n);
   st.n_text += n;
   st.len += n;
+}
+
+// A run of n text tokens; with_vision: registered by the launch that registered the vision run in front of them.
+void note_text_registered(sv::StreamState& st, int n, bool cs_tab_valid, bool with_vision) {
+  st.cs_row0 = with_vision ? st.pending_n : 0;
+  st.ahead = 0;
+  note_text(st, n, cs_tab_valid, !with_vision);
+}
+
+// The next decoded token of each of n_list distinct streams, which have room for it: registered by a launch where an earlier one
+// has not done so already.
+hipError_t register_tokens(sv_cache* c, const int32_t* streams, int n_list, hipStream_t s) {
+  constexpr int kGroup = 64;
+  for (int b0 = 0; b0 < n_list; b0 += kGroup) {
+    int32_t fresh[kGroup];
+    int n_fresh = 0;
+    int64_t n = sv::kAhead;
+    for (int b = b0; b < std::min(n_list, b0 + kGroup); ++b) {
+      const sv::StreamState& st = c->st[streams[b]];
+      if (st.ahead > 0) continue;
+      fresh[n_fresh++] = streams[b];
+      n = std::min(n, c->cfg.capacity_tokens - st.len);
+    }
+    if (n_fresh == 0) continue;
+    if (!c->host_logic_only) {
+      const hipError_t e = sv::launch_meta_tokens(c, fresh, n_fresh, (int)n, s);
+      if (e != hipSuccess) return e;
+    }
+    for (int b = 0; b < n_fresh; ++b) {
+      sv::StreamState& st = c->st[fresh[b]];
+      st.ahead = st.ahead_of = (int)n;
+      st.next_parity ^= 1;
+    }
+  }
+  for (int b = 0; b < n_list; ++b) {
+    sv::StreamState& st = c->st[streams[b]];
+    st.cs_row = st.ahead_of - st.ahead--;
+    st.cs_row0 = 0;
+    note_text(st, 1, false, false);
+  }
+  return hipSuccess;
 }
 
 #define SV_HIP(expr)                         \
@@ -354,6 +395,7 @@ static int append_impl(sv_cache* c, int stream_id, int layer, int n, const uint8
                                     has_blk ? st.next_blk : -1, gT, gH, gW, with_cs, s));
       st.next_parity ^= 1;
     }
+    st.ahead = 0;
     st.cs_tab_valid = with_cs, st.cs_row0 = 0;
     st.pending_slot0 = st.len;
     st.pending_n = n;
@@ -429,6 +471,7 @@ static int evict_impl(sv_cache* c, int stream_id, int64_t n_sink, int64_t vision
   st.front = gone;
   st.cur ^= 1;
   st.next_parity ^= 1;
+  st.ahead = 0;
   st.text_iv.swap(iv_new);
   st.vis_lo = vis_lo_new;
   st.len = n_new;
@@ -535,10 +578,9 @@ int sv_decode_step(sv_cache* c, int layer, const int32_t* stream_ids_host, int n
       return SV_ERR_STATE;
     }
   }
-  if (layer == 0) SV_DEV(sv::launch_meta_tokens(c, stream_ids_host, n_list, s));
+  if (layer == 0) SV_HIP(register_tokens(c, stream_ids_host, n_list, s));
   for (int b = 0; b < n_list; ++b) {
     sv::StreamState& st = c->st[stream_ids_host[b]];
-    if (layer == 0) note_text_registered(st, 1, false);
     st.layer_len[layer] = st.len;
   }
   if (use_mfma) SV_DEV(sv::launch_attn_decode_mfma(c, layer, stream_ids_host, n_list, 1, q_dev, k_dev, v_dev, o_dev, s));
@@ -558,8 +600,7 @@ int sv_decode_step_layers(sv_cache* c, int stream_id, const void* q_dev, const v
   if (st.len + 1 > c->cfg.capacity_tokens) return SV_ERR_CAPACITY;
   hipStream_t s = (hipStream_t)hip_stream;
   const int32_t sid = stream_id;
-  SV_DEV(sv::launch_meta_tokens(c, &sid, 1, s));
-  note_text_registered(st, 1, false);
+  SV_HIP(register_tokens(c, &sid, 1, s));
   for (int l = 0; l < L; ++l) st.layer_len[l] = st.len;
   SV_DEV(sv::launch_attn_decode_mfma(c, -1, &sid, L, 1, q_dev, k_dev, v_dev, o_dev, s));
   return SV_OK;
@@ -681,7 +722,7 @@ int sv_cache_retained(sv_cache* c, int stream_id, int64_t* ids_host, int32_t* po
     SV_HIP(hipMemcpyAsync(pos.data(), c->meta[st.cur].pos4 + off, (size_t)n * 16, hipMemcpyDeviceToHost, s));
   }
   SV_HIP(hipStreamSynchronize(s));
-  if ((int64_t)n_dev != st.len) return SV_ERR_STATE;   // host bookkeeping and device scan disagree
+  if ((int64_t)n_dev != st.len + st.ahead) return SV_ERR_STATE;   // host bookkeeping and device scan disagree
   if (n > 0 && pos3_host)
     for (int64_t i = 0; i < n; ++i) {
       pos3_host[3 * i + 0] = pos[i].x;

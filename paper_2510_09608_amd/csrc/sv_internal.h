@@ -40,6 +40,8 @@ struct MetaPtrs {
   uint8_t* type;
 };
 
+constexpr int kAhead = 16;   // decoded tokens registered by one launch (see k_meta_tokens)
+
 struct StreamState {
   int64_t len = 0;        // tokens in cache
   int64_t n_text = 0;     // text tokens ever appended
@@ -48,6 +50,9 @@ struct StreamState {
   int32_t next_blk = 0;
   int cur = 0;            // which half of the ping-pong store is live
   int next_parity = 0;    // which entry of next_pos[stream][2] is live
+  // Decoded tokens are registered up to kAhead at a time (launch_meta_tokens): of the last ahead_of `ahead` are registered beyond
+  // len, and the newest token of the stream, if it was decoded, has row cs_row of last_cs.
+  int ahead = 0, ahead_of = 0, cs_row = 0;
   int64_t vis_lo = 0;     // vision ranks present are [vis_lo, n_vis)
   std::vector<std::pair<int64_t, int64_t>> text_iv;  // text ranks present, disjoint half-open intervals
   std::vector<int64_t> layer_len;                    // tokens stored per layer
@@ -91,10 +96,11 @@ struct sv_cache {
   int32_t* src;              // device [n_streams][capacity]   gather list of the last eviction
   int32_t* turn;             // device [n_streams][capacity]   re-rotation of the last eviction: 1 + row of dtab, 0: none
   float2* dtab;              // device [n_streams][capacity][head_dim/2]  cos/sin of position shifts, row = a slot that has it
-  int32_t* next_pos;         // device [n_streams][2]          scalar position of the next token (ping-pong)
-  int32_t* n_dev;            // device [n_streams]             retained count written by the scan
+  int32_t* next_pos;         // device [n_streams][2]          scalar position of the next token to register (ping-pong)
+  int32_t* n_dev;            // device [n_streams]             registered tokens (the stream's, and those registered ahead)
   double* inv_freq;          // device [head_dim/2]
-  float2* last_cs;           // device [n_streams][head_dim/2]  cos/sin at the position of the newest token
+  float2* last_cs;           // device [n_streams][kAhead][head_dim/2]  cos/sin at the positions of the decoded tokens that
+                             // were registered together
   float2* cs_tab;            // device [n_streams][cs_rows][head_dim/2]  cos/sin of the tokens of the last
                              // registered run (written when it has at most max_q_tokens tokens)
   int64_t cs_rows;           // max_q_tokens + kTextRows
@@ -116,6 +122,8 @@ struct sv_cache {
   std::vector<sv::StreamState> st;
   mutable sv::ChunkPlan chunk_plan, store_plan;   // host only; a handle is used by one thread at a time
 
+  // cos/sin at the position of the stream's newest token, a decoded one
+  float2* token_cs(int stream) const { return last_cs + ((size_t)stream * sv::kAhead + st[stream].cs_row) * (cfg.head_dim / 2); }
   // cos/sin of the pending run's tokens
   float2* run_cs(int stream) const { return cs_tab + ((size_t)stream * cs_rows + st[stream].cs_row0) * (cfg.head_dim / 2); }
   char* kv_ptr(int stream, int half, int layer, int which) const {
@@ -136,13 +144,15 @@ struct TypeMask {
 };
 
 // type_uniform: SV_TEXT / SV_VISION when all n tokens share it, -1 to read `mask`.
-// with_cs_tab: also write the rotary cos/sin of the n tokens to c->cs_tab (n <= max_q_tokens).
+// with_cs_tab: also write the rotary cos/sin of the n tokens to c->cs_tab (n <= max_q_tokens).  Tokens that are registered ahead
+// are taken back.
 hipError_t launch_meta_append(const sv_cache* c, int stream, int next_parity, int64_t slot0, int n,
                               int64_t gid0, int64_t rank_text0, int64_t rank_vis0, int type_uniform,
                               const TypeMask* mask, int blk, int gT, int gH, int gW, bool with_cs_tab, hipStream_t s);
 
-// The same for one new text token (slot = the stream's length) of each of n_list distinct streams, in one launch.
-hipError_t launch_meta_tokens(const sv_cache* c, const int32_t* streams, int n_list, hipStream_t s);
+// The same for the next n_ahead (1 .. kAhead) text tokens (from slot = the stream's length on) of each of n_list distinct streams
+// that have none registered ahead, in one launch.
+hipError_t launch_meta_tokens(const sv_cache* c, const int32_t* streams, int n_list, int n_ahead, hipStream_t s);
 
 // A second's two runs, registered by the eviction in front of them: n_vision vision tokens of one grid behind the n_kept
 // survivors, then n_text text tokens, at most kTextRows, whose cos/sin rows follow the vision tokens' in cs_tab.

@@ -58,21 +58,14 @@ __device__ __forceinline__ int angle_pos(int64_t slot0, int j, int i, int next, 
 __global__ void k_meta_append(MetaPtrs m, const int32_t* __restrict__ next_in, int32_t* __restrict__ next_out,
                               int64_t slot0, int n, int64_t gid0, int64_t rank_text0, int64_t rank_vis0,
                               int type_uniform, TypeMask mask, int rope3d, int blk, int gT, int gH, int gW,
-                              float2* __restrict__ last_cs, const double* __restrict__ inv_freq, int half,
-                              int rope_none, int s0, int s01, int f32_data, int32_t* __restrict__ n_dev,
-                              float2* __restrict__ cs_tab) {
+                              const double* __restrict__ inv_freq, int half, int s0, int s01, int f32_data, int32_t* __restrict__ n_dev,
+                              float2* __restrict__ cs_tab, int ahead) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  const int next = *next_in;
+  const int next = *next_in - ahead;   // text tokens that were registered ahead are taken back
   if (cs_tab != nullptr && j < n * half) {
     // cos/sin of every new token's rotary angles (thread = one token, one frequency)
     const int tok = j / half, i = j % half;
     cs_tab[j] = angle_cs(angle_pos(slot0, tok, i, next, rope3d, blk, gH, gW, s0, s01), inv_freq[i], f32_data);
-  }
-  if (blockIdx.x == 0 && threadIdx.x < half) {
-    // cos/sin of the rotary angles of the LAST token of this append (the decode kernel's query token)
-    const int i = threadIdx.x;
-    last_cs[i] = rope_none ? make_float2(1.f, 0.f)
-                           : angle_cs(angle_pos(slot0, n - 1, i, next, rope3d, blk, gH, gW, s0, s01), inv_freq[i], f32_data);
   }
   if (j == 0) {
     int adv;
@@ -99,9 +92,13 @@ __global__ void k_meta_append(MetaPtrs m, const int32_t* __restrict__ next_in, i
 }
 
 // ---------------------------------------------------------------------------------
-// One new text token for each of several streams (a decode step of a batch): what k_meta_append writes for n = 1, one
-// workgroup of one wavefront per stream, so that a step of 16 streams costs one launch and not 16 in a row (2.1 us and a
-// gap each: 0.7 of the 3.4 ms that a second of 16 ragged streams took at 4 layers).
+// The next n_ahead text tokens of each of several streams (decode steps of a batch): what k_meta_append writes for a run of them,
+// one workgroup of one wavefront per stream and token, so that a step of 16 streams costs one launch and not 16 in a row (2.1 us
+// and a gap each: 0.7 of the 3.4 ms that a second of 16 ragged streams took at 4 layers).  What a decoded token's registration
+// writes (arrival id, rank, position, rotary cos/sin) follows from the stream's counts alone, so kAhead steps share one launch: the
+// steps behind the first find their token registered unless the stream was appended to or evicted in between, which starts from
+// the tokens that are really there.  A launch in every step, back to back with the attention, took 5.1 us: 16 ragged
+// streams, 4 layers, 16 tokens 2714 -> 2657 us; one stream, 28 layers, 256 vision and 16 text tokens layer by layer 3811 -> 3770.
 // ---------------------------------------------------------------------------------
 struct TokenRow {
   int64_t gid, rank;   // arrival id, rank among the stream's text tokens
@@ -117,23 +114,25 @@ __global__ __launch_bounds__(64) void k_meta_tokens(MetaPtrs m0, MetaPtrs m1, in
                                                     int32_t* __restrict__ n_dev, int64_t capacity, int half, int rope3d,
                                                     int rope_none, int f32_data, TokenTable tab) {
   const TokenRow r = tab.r[blockIdx.x];
-  const int sid = r.stream >> 2, parity = r.stream & 1, lane = threadIdx.x;
+  const int sid = r.stream >> 2, parity = r.stream & 1, lane = threadIdx.x, j = blockIdx.y, n_ahead = gridDim.y;
   const int next = next_pos[2 * sid + parity];
-  const int p = rope3d ? next : r.slot;   // 1-D: position == slot
+  const int p = (rope3d ? next : r.slot) + j;   // 1-D: position == slot
   if (lane < half) {
-    last_cs[(size_t)sid * half + lane] = rope_none ? make_float2(1.f, 0.f) : angle_cs(p, inv_freq[lane], f32_data);
+    last_cs[((size_t)sid * kAhead + j) * half + lane] = rope_none ? make_float2(1.f, 0.f) : angle_cs(p, inv_freq[lane], f32_data);
   }
   if (lane == 0) {
     const bool second = (r.stream & 2) != 0;
-    const int64_t at = (int64_t)sid * capacity + r.slot;
-    (second ? m1.gid : m0.gid)[at] = r.gid;
-    (second ? m1.rank : m0.rank)[at] = r.rank;
+    const int64_t at = (int64_t)sid * capacity + r.slot + j;
+    (second ? m1.gid : m0.gid)[at] = r.gid + j;
+    (second ? m1.rank : m0.rank)[at] = r.rank + j;
     (second ? m1.type : m0.type)[at] = (uint8_t)SV_TEXT;
     (second ? m1.blk : m0.blk)[at] = -1;
     (second ? m1.local4 : m0.local4)[at] = make_short4(0, 0, 0, 1);
     (second ? m1.pos4 : m0.pos4)[at] = make_int4(p, p, p, p);
-    next_pos[2 * sid + (parity ^ 1)] = p + 1;
-    n_dev[sid] = r.slot + 1;   // the device's own token count
+    if (j == n_ahead - 1) {
+      next_pos[2 * sid + (parity ^ 1)] = p + 1;
+      n_dev[sid] = r.slot + n_ahead;   // the device's own token count
+    }
   }
 }
 
@@ -204,7 +203,7 @@ struct Registration {
   int n_reg;
   NewRuns runs;
   int rope3d, s0, s01;
-  float2 *cs_tab, *last_cs;
+  float2* cs_tab;
 };
 
 template <typename... R>
@@ -413,13 +412,7 @@ __global__ __launch_bounds__(kScanThreads) void k_evict_scan(MetaPtrs in, MetaPt
                       g.rope3d, -1, 1, 1, 1);
       }
       if (dtab != nullptr)
-        for (int x = at; x < new_cnt * half; x += step) {
-          const float2 cs = cs_of(x / half, x % half);
-          g.cs_tab[x] = cs;
-          if (x / half == new_cnt - 1) g.last_cs[x % half] = cs;
-        }
-      else if (at < half)
-        g.last_cs[at] = make_float2(1.f, 0.f);
+        for (int x = at; x < new_cnt * half; x += step) g.cs_tab[x] = cs_of(x / half, x % half);
     }
   }
   if (w == (int)gridDim.x - 1) {
@@ -448,14 +441,14 @@ hipError_t launch_meta_append(const sv_cache* c, int stream, int next_parity, in
   int32_t* nout = c->next_pos + 2 * stream + (next_parity ^ 1);
   hipLaunchKernelGGL(k_meta_append, dim3(blocks), dim3(threads), 0, s, m, nin, nout, slot0, n, gid0, rank_text0,
                      rank_vis0, type_uniform, mk, c->cfg.rope_mode == SV_ROPE_3D ? 1 : 0, blk, gT, gH, gW,
-                     c->last_cs + (size_t)stream * half, c->inv_freq, half, c->cfg.rope_mode == SV_ROPE_NONE ? 1 : 0,
+                     c->inv_freq, half,
                      c->cfg.mrope_sections[0], c->cfg.mrope_sections[0] + c->cfg.mrope_sections[1],
                      c->cfg.dtype == SV_DTYPE_F32 ? 1 : 0, c->n_dev + stream,
-                     with_cs_tab ? c->cs_tab + (size_t)stream * c->cs_rows * half : nullptr);
+                     with_cs_tab ? c->cs_tab + (size_t)stream * c->cs_rows * half : nullptr, c->st[stream].ahead);
   return hipGetLastError();
 }
 
-hipError_t launch_meta_tokens(const sv_cache* c, const int32_t* streams, int n_list, hipStream_t s) {
+hipError_t launch_meta_tokens(const sv_cache* c, const int32_t* streams, int n_list, int n_ahead, hipStream_t s) {
   for (int r0 = 0; r0 < n_list; r0 += kMaxTokenRows) {
     const int nr = std::min(kMaxTokenRows, n_list - r0);
     TokenTable tab;
@@ -464,7 +457,7 @@ hipError_t launch_meta_tokens(const sv_cache* c, const int32_t* streams, int n_l
       const StreamState& st = c->st[sid];
       tab.r[b] = {st.next_gid, st.n_text, (int32_t)st.len, sid << 2 | st.cur << 1 | st.next_parity};
     }
-    hipLaunchKernelGGL(k_meta_tokens, dim3(nr), dim3(64), 0, s, c->meta[0], c->meta[1], c->next_pos, c->last_cs,
+    hipLaunchKernelGGL(k_meta_tokens, dim3(nr, n_ahead), dim3(64), 0, s, c->meta[0], c->meta[1], c->next_pos, c->last_cs,
                        c->inv_freq, c->n_dev, c->cfg.capacity_tokens, c->cfg.head_dim / 2,
                        c->cfg.rope_mode == SV_ROPE_3D ? 1 : 0, c->cfg.rope_mode == SV_ROPE_NONE ? 1 : 0,
                        c->cfg.dtype == SV_DTYPE_F32 ? 1 : 0, tab);
@@ -497,8 +490,7 @@ hipError_t launch_evict_scan(const sv_cache* c, int stream, int next_parity, int
   if (runs)
     launch(k_evict_scan<Registration>,
            Registration{n_reg, *runs, c->cfg.rope_mode == SV_ROPE_3D ? 1 : 0, c->cfg.mrope_sections[0],
-                        c->cfg.mrope_sections[0] + c->cfg.mrope_sections[1], c->cs_tab + (size_t)stream * c->cs_rows * half,
-                        c->last_cs + (size_t)stream * half});
+                        c->cfg.mrope_sections[0] + c->cfg.mrope_sections[1], c->cs_tab + (size_t)stream * c->cs_rows * half});
   else
     launch(k_evict_scan<>);
   return hipGetLastError();

@@ -865,3 +865,88 @@ def test_decode_ranges_whose_wavefronts_have_one_tile_or_none(dtype, hq, hkv, d,
             ref = orc.gqa_attention(f64(q[m - 1:m]), f64(k[:m]), f64(v[:m]), np.array([m - 1]), True)
             assert gu.max_err(gu.host(od), ref) <= gu.TOL[dtype]
         assert np.array_equal(cache.read_kv(b, 0, 0, n, 1), k[n:n + 1]) and np.array_equal(cache.read_kv(b, 0, 1, n, 1), v[n:n + 1])
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d,mode,flags", [
+    ("bf16", 4, 2, 128, sv.SV_ROPE_3D, 0), ("bf16", 4, 4, 64, sv.SV_ROPE_1D, 0), ("f32", 2, 1, 64, sv.SV_ROPE_3D, 0),
+    ("bf16", 4, 2, 128, sv.SV_ROPE_3D, sv.SV_FLAG_GENERIC_KERNELS), ("f32", 4, 2, 128, sv.SV_ROPE_1D, sv.SV_FLAG_GENERIC_KERNELS)])
+def test_decoded_tokens_registered_ahead(dtype, hq, hkv, d, mode, flags):
+    """Decode steps of three streams that fall out of step with each other, past one registration's tokens and up to the end of the
+    capacity, with appends, evictions (one that does nothing) and seconds in between, against append, rope_apply and attn_decode:
+    ids, positions (of the device's own count), stored rows and outputs."""
+    sec = ((16, 24, 24) if d == 128 else (8, 12, 12)) if mode == sv.SV_ROPE_3D else (0, 0, 0)
+    dt, code = (torch.float32, sv.SV_DTYPE_F32) if dtype == "f32" else (torch.bfloat16, sv.SV_DTYPE_BF16)
+    cap = 70
+    a, b = (sv.Cache(2, hq, hkv, d, code, mode, 1e4, sec, 3, cap, 24, flags=flags) for _ in range(2))
+    g = torch.Generator(device="cuda:0").manual_seed(78)
+    rnd = lambda *shape: torch.randn(*shape, device="cuda:0", generator=g).to(dt)
+
+    def append(s, n, thw=None):
+        types = np.full(n, sv.SV_TEXT if thw is None else sv.SV_VISION, np.uint8)
+        k, v = rnd(2, n, hkv, d), rnd(2, n, hkv, d)
+        for c in (a, b):
+            for layer in range(2):
+                c.append(s, layer, types if layer == 0 else None, thw if layer == 0 else None, k[layer], v[layer])
+
+    def step(ids):
+        q, k, v = rnd(2, len(ids), hq, d), rnd(2, len(ids), hkv, d), rnd(2, len(ids), hkv, d)
+        oa, ob = torch.empty_like(q), torch.empty_like(q)
+        for layer in range(2):
+            a.decode_step(layer, ids, q[layer], k[layer], v[layer], oa[layer])
+            for i, s in enumerate(ids):
+                b.append(s, layer, np.zeros(1, np.uint8) if layer == 0 else None, None, k[layer, i:i + 1], v[layer, i:i + 1])
+            for i, s in enumerate(ids):
+                b.rope_apply(s, b.len(s) - 1, 1, q[layer, i:i + 1], None)
+            b.attn_decode(layer, ids, q[layer], ob[layer])
+        # (each is within the tolerance of the exact result)
+        assert gu.max_err(gu.host(oa), gu.host(ob)) <= 2 * gu.TOL[dtype]
+
+    def second(s):
+        n, t = 6, 2
+        q, k, v = rnd(2, n, hq, d), rnd(2, n, hkv, d), rnd(2, n, hkv, d)
+        qt, kt, vt = rnd(t, 2, 1, hq, d), rnd(t, 2, 1, hkv, d), rnd(t, 2, 1, hkv, d)
+        for c in (a, b):
+            c.stream_step(s, 4, 12, 9, q_vision=q.clone(), k_vision=k, v_vision=v, o_vision=torch.empty_like(q), grid_thw=(1, 2, 3),
+                          q_text=qt, k_text=kt, v_text=vt, o_text=torch.empty_like(qt))
+
+    def check(what):
+        print(f"{dtype} d{d} mode {mode} flags {flags}: {what}", flush=True)
+        for s in range(3):
+            n = a.len(s)
+            assert n == b.len(s)
+            for x, y in zip(a.retained(s), b.retained(s)):
+                assert np.array_equal(x, y)
+            for layer in range(2):
+                for which in range(2):
+                    # (K: one rounding of the rotation where the two kernels order it differently)
+                    x, y = a.read_kv(s, layer, which, 0, n), b.read_kv(s, layer, which, 0, n)
+                    assert np.allclose(x, y, rtol=0 if which else (2.0 ** -7 if dtype == "bf16" else 1e-5), atol=0 if which else 1e-6)
+
+    for s, n in enumerate((5, 9, 1)):
+        append(s, n)
+        append(s, 12, (2, 2, 3))
+    for ids in ([0], [1, 0], [2, 0, 1], [2]):
+        step(ids)
+    check("out of step")
+    append(0, 3)
+    append(1, 6, (1, 3, 2))
+    step([0, 1, 2])
+    check("appended to")
+    assert [c.evict(2, 100, 100, 100) for c in (a, b)] == [a.len(2)] * 2   # nothing leaves
+    assert a.evict(1, 2, 7, 3) == b.evict(1, 2, 7, 3)
+    step([2, 1])
+    check("evicted")
+    second(0)
+    step([0])
+    step([1, 0])
+    check("a second")
+    for _ in range(18):
+        step([2, 1])
+    check("past one registration")
+    for s in (2, 0):
+        while a.len(s) < cap:
+            step([s])
+    check("full")
+    with pytest.raises(sv.SvError):
+        step([0, 1])
+    check("refused")
