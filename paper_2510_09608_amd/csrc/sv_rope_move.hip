@@ -165,13 +165,54 @@ __device__ __forceinline__ void rope_rows(int bx, T* __restrict__ x, const int4*
   *(decltype(hi.raw)*)(p + D / 2 + t * G::EPV) = hi.raw;
 }
 
-// grid: ceil(n * n_heads / ROWS).  cs_tab: of the run that starts at slot0, or NULL.
-template <typename T, int D>
+// The same as a launch of its own.  A thread takes its place of HG heads of a token: position, cos/sin and what is divided are worked
+// out once for them, below the rows' loads.  With a head per thread, and the token from a 64-bit division, the launch was bound by
+// that: 5376 tokens of 28 heads (77 MB) 17.2 us, with 4 heads 13.0 (5.9 TB/s).
+// grid: ceil(n / ROWS) * ceil(n_heads / HG), the heads' shares side by side.  cs_tab: of the run that starts at slot0, or NULL.
+template <typename T, int D, int HG>
 __global__ __launch_bounds__(256) void k_rope_rows(T* __restrict__ x, const int4* __restrict__ pos4,
                                                    const double* __restrict__ inv_freq, int64_t slot0, int n,
                                                    int n_heads, int rope_mode, int s0, int s01,
                                                    const float2* __restrict__ cs_tab) {
-  rope_rows<T, D>(blockIdx.x, x, pos4, inv_freq, slot0, n, n_heads, rope_mode, s0, s01, cs_tab);
+  using G = RowGeom<T, D>;
+  constexpr int E = Vec16<T>::N;
+  const uint32_t shares = (uint32_t)(n_heads + HG - 1) / HG, tokens = blockIdx.x / shares, share = blockIdx.x - tokens * shares;
+  const int j = tokens * G::ROWS + threadIdx.x / G::TPR, t = threadIdx.x % G::TPR;
+  if (j >= n) return;
+  T* const p = x + ((size_t)j * n_heads + HG * share) * D + t * G::EPV;
+  const int heads = min(HG, n_heads - (int)(HG * share));
+  Vec16<T> lo[HG], hi[HG];
+#pragma unroll
+  for (int h = 0; h < HG; ++h) {
+    const T* const row = p + min(h, heads - 1) * D;
+    lo[h].raw = *(const decltype(lo[h].raw)*)row;
+    hi[h].raw = *(const decltype(hi[h].raw)*)(row + D / 2);
+  }
+  float2 r[E];
+  if (cs_tab != nullptr) {   // cos/sin of the run's tokens, tabulated when it was registered: [token][pair]
+    const float2* cs = cs_tab + (size_t)j * (D / 2) + t * G::EPV;
+#pragma unroll
+    for (int e = 0; e < E; ++e) r[e] = cs[e];
+  } else {
+    const int4 pos = pos4[slot0 + j];
+    double f[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) f[e] = inv_freq[t * G::EPV + e];
+#pragma unroll
+    for (int e = 0; e < E; ++e) rot_cs<T>((double)pos_of_freq(pos, t * G::EPV + e, rope_mode, s0, s01) * f[e], r[e].x, r[e].y);
+  }
+#pragma unroll
+  for (int h = 0; h < HG; ++h) {
+    if (h >= heads) break;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const float a = lo[h].get(e), b = hi[h].get(e);
+      lo[h].set(e, a * r[e].x - b * r[e].y);
+      hi[h].set(e, b * r[e].x + a * r[e].y);
+    }
+    *(decltype(lo[h].raw)*)(p + h * D) = lo[h].raw;
+    *(decltype(hi[h].raw)*)(p + h * D + D / 2) = hi[h].raw;
+  }
 }
 
 // Everything that stores a run of new tokens of one layer in a row-major cache, in ONE launch: workgroup ids [0, nb_k)
@@ -503,10 +544,17 @@ hipError_t rope_apply_t(const sv_cache* c, int stream, int64_t slot0, int n, voi
   const int heads[2] = {c->cfg.n_q_heads, c->cfg.n_kv_heads};
   for (int a = 0; a < 2; ++a) {
     if (!ptrs[a]) continue;
-    const int64_t rows = (int64_t)n * heads[a];
-    dim3 grid((unsigned)((rows + G::ROWS - 1) / G::ROWS));
-    hipLaunchKernelGGL((k_rope_rows<T, D>), grid, dim3(256), 0, s, (T*)ptrs[a], c->meta[cur].pos4 + off,
-                       c->inv_freq, slot0, n, heads[a], c->cfg.rope_mode, s0, s01, run_table(c, stream, slot0, n));
+    auto launch = [&](auto kernel, int hg) {
+      const int64_t groups = (int64_t)((n + G::ROWS - 1) / G::ROWS) * ((heads[a] + hg - 1) / hg);
+      hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(256), 0, s, (T*)ptrs[a], c->meta[cur].pos4 + off, c->inv_freq, slot0, n,
+                         heads[a], c->cfg.rope_mode, s0, s01, run_table(c, stream, slot0, n));
+    };
+    // The more heads per thread that leave some 400 workgroups (us, 1, 2 and 4 heads: 2000 x 28 8.2, 7.75 and 7.5, 5000 x 8 6.3, 6.25 and
+    // 6.6, 3000 x 12 6.1, 6.0 and 6.1, 700 x 28 4.4, 4.2 and 4.2).
+    const int64_t full = (int64_t)n * heads[a] / G::ROWS;
+    if (full >= 1600) launch(k_rope_rows<T, D, 4>, 4);
+    else if (full >= 600) launch(k_rope_rows<T, D, 2>, 2);
+    else launch(k_rope_rows<T, D, 1>, 1);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -997,3 +997,23 @@ def test_chunk_merge_of_few_and_of_many_ranges(hq, hkv, d, n_q, n_kv):
             od = torch.full_like(qd, float("nan"))
             cache.attn_chunk(0, 0, qd, od, causal)
             assert gu.max_err(gu.host(od), ref) <= gu.TOL["bf16"]
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+@pytest.mark.parametrize("hq,n", [(28, 1843), (30, 700), (7, 2750), (1, 33)])
+def test_rotation_of_long_runs(dtype, d, hq, n):
+    """Rows rotated one, two and four heads to a thread, with and without the run's table, heads that fill the last share and that do
+    not: bit for bit what pieces of 31 tokens give, whose heads go one by one."""
+    dt, code = (torch.float32, sv.SV_DTYPE_F32) if dtype == "f32" else (torch.bfloat16, sv.SV_DTYPE_BF16)
+    g = torch.Generator(device="cuda:0").manual_seed(hq)
+    q, k = (torch.randn(n, h, d, device="cuda:0", generator=g).to(dt) for h in (hq, 1))
+    for max_q in (n, 8):
+        print(f"{dtype} d{d} {hq} heads n={n} max_q={max_q}", flush=True)
+        cache = sv.Cache(1, hq, 1, d, code, sv.SV_ROPE_3D, 1e6, (16, 24, 24) if d == 128 else (8, 12, 12), 1, n, max_q)
+        cache.append(0, 0, np.zeros(n, np.uint8), None, k, k)
+        x, y, kx, ky = q.clone(), q.clone(), k.clone(), k.clone()
+        cache.rope_apply(0, 0, n, x, kx)
+        for j in range(0, n, 31):
+            m = min(31, n - j)
+            cache.rope_apply(0, j, m, y[j:j + m], ky[j:j + m])
+        assert torch.equal(x, y) and torch.equal(kx, ky) and not torch.equal(x, q)
