@@ -1017,3 +1017,24 @@ def test_rotation_of_long_runs(dtype, d, hq, n):
             m = min(31, n - j)
             cache.rope_apply(0, j, m, y[j:j + m], ky[j:j + m])
         assert torch.equal(x, y) and torch.equal(kx, ky) and not torch.equal(x, q)
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (2, 1, 64), (9, 3, 64), (5, 5, 128)])
+@pytest.mark.parametrize("n_q,n_kv", [(1, 1100), (9, 2100), (70, 2200), (200, 300)])
+def test_fp32_chunk_merge_of_few_and_of_many_ranges(hq, hkv, d, n_q, n_kv):
+    """fp32 chunks in 2 to 64 key ranges, one, two and four groups of lanes to a row, whole passes and not, heads that fill a workgroup
+    and that do not, causal rows that see only some of the ranges, against the oracle."""
+    w = si.Workload("m", 1, hq, hkv, d, "f32", 2, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, 772)
+    cache = sv.Cache(1, hq, hkv, d, sv.SV_DTYPE_F32, sv.SV_ROPE_NONE, 1e4, (0, 0, 0), 1, n_kv, n_q)
+    q, k, v = w.qkv(0, np.arange(n_kv))
+    q = q[n_kv - n_q:]
+    cache.append(0, 0, np.zeros(n_kv, dtype=np.uint8), None, gu.dev(k, w), gu.dev(v, w))
+    qd = gu.dev(q, w)
+    for causal in (True, False):
+        ref = orc.gqa_attention(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), np.arange(n_kv - n_q, n_kv), causal)
+        for splits in (0, 2, 7, 8, 9, 15, 16, 17, 31, 34, 64):
+            print(f"f32 {hq}/{hkv} x {d} n_q={n_q} n_kv={n_kv} causal={causal} splits={splits}", flush=True)
+            cache.set_option(sv.SV_OPT_CHUNK_SPLITS, splits)
+            od = torch.full_like(qd, float("nan"))
+            cache.attn_chunk(0, 0, qd, od, causal)
+            assert gu.max_err(gu.host(od), ref) <= gu.TOL["f32"]
