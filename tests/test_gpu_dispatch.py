@@ -1038,3 +1038,37 @@ def test_fp32_chunk_merge_of_few_and_of_many_ranges(hq, hkv, d, n_q, n_kv):
             od = torch.full_like(qd, float("nan"))
             cache.attn_chunk(0, 0, qd, od, causal)
             assert gu.max_err(gu.host(od), ref) <= gu.TOL["f32"]
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(28, 4, 128), (16, 2, 64), (3, 3, 128), (4, 1, 64)])
+@pytest.mark.parametrize("layers", [1, 24])
+def test_decode_batches_whose_wavefronts_have_one_tile_or_none(hq, hkv, d, layers):
+    """Batches of one block of 128 keys per workgroup, rows of one to four of them, the last with one to four tiles, whole or a key more or
+    less: attention alone and fused steps, whose token is in the last tile or is a tile or a block of its own.  With few layers K goes
+    through LDS; with many it comes straight into registers where a launch reads more than 6.5 MB (head_dim 128)."""
+    lens = [128 * a + m for a in range(4) for m in (1, 31, 32, 33, 127, 128)] if layers == 1 else [504] * 3 + [1633, 1600, 127]
+    w = si.Workload("o", 1, hq, hkv, d, "bf16", 2, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, 9998)
+    cache = sv.Cache(layers, hq, hkv, d, sv.SV_DTYPE_BF16, sv.SV_ROPE_NONE, 1e4, (0, 0, 0), len(lens), max(lens) + 8, 16)
+    q, k, v = w.qkv(0, np.arange(max(lens) + 1))
+    f64 = lambda x: x.astype(np.float64)
+    ids = list(range(len(lens)))
+    kd, vd = gu.dev(k, w), gu.dev(v, w)
+    for b, n in enumerate(lens):
+        for layer in range(layers):
+            cache.append(b, layer, np.zeros(n, np.uint8) if layer == 0 else None, None, kd[:n], vd[:n])
+    for new in (False, True):
+        print(f"{hq}/{hkv} x {d} layers={layers} new={new}", flush=True)
+        at = [n - 1 + new for n in lens]
+        for layer in range(layers):
+            od = torch.full((len(lens), hq, d), float("nan"), device="cuda:0", dtype=torch.bfloat16)
+            if new:
+                cache.decode_step(layer, ids, gu.dev(q[at], w), gu.dev(k[at], w), gu.dev(v[at], w), od)
+            else:
+                cache.attn_decode(layer, ids, gu.dev(q[at], w), od)
+            if layer in (0, layers - 1):
+                for b, p in enumerate(at):
+                    ref = orc.gqa_attention(f64(q[p:p + 1]), f64(k[:p + 1]), f64(v[:p + 1]), np.array([p]), True)
+                    assert gu.max_err(gu.host(od[b:b + 1]), ref) <= gu.TOL["bf16"]
+    for b, n in enumerate(lens):
+        for which, x in ((0, k), (1, v)):
+            assert np.array_equal(cache.read_kv(b, layers - 1, which, n, 1), x[n:n + 1])
