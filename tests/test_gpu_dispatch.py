@@ -954,32 +954,6 @@ def test_decoded_tokens_registered_ahead(dtype, hq, hkv, d, mode, flags):
 
 @pytest.mark.parametrize("hq,hkv,d", [(28, 4, 128), (16, 2, 64), (3, 3, 128), (8, 1, 64)])
 @pytest.mark.parametrize("n_q,n_kv", [(1, 2100), (5, 4200), (37, 4300), (73, 2200), (200, 1100), (300, 700)])
-def test_chunk_merge_shared_out_and_left_to_late_workgroups(hq, hkv, d, n_q, n_kv):
-    """Chunks in 2 to 64 key ranges, whose workgroups share out the rows of the merge (whole rows each, or several groups of lanes to a
-    row; row tiles that are full, ragged or a few rows; causal ones that see only some of the ranges), against the oracle; and the same
-    with every workgroup that comes early leaving its share to the last, bit for bit, launch after launch."""
-    w = si.Workload("m", 1, hq, hkv, d, "bf16", 2, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, 771)
-    cache = sv.Cache(1, hq, hkv, d, sv.SV_DTYPE_BF16, sv.SV_ROPE_NONE, 1e4, (0, 0, 0), 1, n_kv, n_q)
-    q, k, v = w.qkv(0, np.arange(n_kv))
-    q = q[n_kv - n_q:]
-    cache.append(0, 0, np.zeros(n_kv, dtype=np.uint8), None, gu.dev(k, w), gu.dev(v, w))
-    qd = gu.dev(q, w)
-    for causal in (True, False):
-        ref = orc.gqa_attention(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), np.arange(n_kv - n_q, n_kv), causal)
-        for splits in (2, 3, 4, 6, 7, 9, 11, 14, 17, 24, 33, 64):
-            print(f"{hq}/{hkv} x {d} n_q={n_q} n_kv={n_kv} causal={causal} splits={splits}", flush=True)
-            cache.set_option(sv.SV_OPT_CHUNK_SPLITS, splits)
-            out = []
-            for looks in (0, sv.SV_MERGE_ONE_LOOK, 0):
-                cache.set_option(sv.SV_OPT_DECODE_TILES_PER_WAVE, looks)
-                out.append(torch.full_like(qd, float("nan")))
-                cache.attn_chunk(0, 0, qd, out[-1], causal)
-            assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
-            assert gu.max_err(gu.host(out[0]), ref) <= gu.TOL["bf16"]
-
-
-@pytest.mark.parametrize("hq,hkv,d", [(28, 4, 128), (16, 2, 64), (3, 3, 128), (8, 1, 64)])
-@pytest.mark.parametrize("n_q,n_kv", [(1, 2100), (5, 4200), (37, 4300), (73, 2200), (300, 700)])
 def test_chunk_merge_of_few_and_of_many_ranges(hq, hkv, d, n_q, n_kv):
     """Chunks in 2 to 64 key ranges, as whole numbers per group of lanes and not, one, two and four groups to a row, heads that fill a
     workgroup's groups and that do not, and causal rows that see only some of the ranges, against the oracle."""
