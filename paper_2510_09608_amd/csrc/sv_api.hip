@@ -55,7 +55,7 @@ bool config_ok(const sv_config* c) {
 // sv_cache_bytes and sv_cache_create cannot disagree.
 struct Layout {
   size_t kv, meta_gid[2], meta_rank[2], meta_pos[2], meta_local[2], meta_blk[2], meta_type[2];
-  size_t src, turn, dtab, next_pos, n_dev, inv_freq, last_cs, cs_tab, part_o, part_ml, counters, part_dec, part_batch, scan_agg, total;
+  size_t src, turn, dtab, next_pos, n_dev, inv_freq, cs_tab, part_o, part_ml, counters, part_dec, part_batch, scan_agg, total;
   int64_t part_rows;
   size_t part_dec_bytes, part_batch_bytes;
 };
@@ -86,7 +86,6 @@ Layout make_layout(const sv_config& c) {
   L.next_pos = take(S * 2 * 4);
   L.n_dev = take(S * 4);
   L.inv_freq = take((size_t)(c.head_dim / 2) * 8);
-  L.last_cs = take(S * (size_t)sv::kAhead * (size_t)(c.head_dim / 2) * 8);
   L.cs_tab = take(S * ((size_t)c.max_q_tokens + sv::kTextRows) * (size_t)(c.head_dim / 2) * 8);
   L.part_rows = std::max<int64_t>(64 * (int64_t)c.n_streams, std::max<int64_t>(4096, 4 * (int64_t)c.max_q_tokens));
   L.part_o = take((size_t)L.part_rows * c.n_q_heads * c.head_dim * 4);
@@ -171,13 +170,13 @@ hipError_t register_tokens(sv_cache* c, const int32_t* streams, int n_list, hipS
     }
     for (int b = 0; b < n_fresh; ++b) {
       sv::StreamState& st = c->st[fresh[b]];
-      st.ahead = st.ahead_of = (int)n;
+      st.ahead = (int)n;
       st.next_parity ^= 1;
     }
   }
   for (int b = 0; b < n_list; ++b) {
     sv::StreamState& st = c->st[streams[b]];
-    st.cs_row = st.ahead_of - st.ahead--;
+    --st.ahead;
     st.cs_row0 = 0;
     note_text(st, 1, false, false);
   }
@@ -273,7 +272,6 @@ int sv_cache_create(const sv_config* cfg, void* dev_arena, size_t arena_bytes, v
   c->next_pos = (int32_t*)(base + L.next_pos);
   c->n_dev = (int32_t*)(base + L.n_dev);
   c->inv_freq = (double*)(base + L.inv_freq);
-  c->last_cs = (float2*)(base + L.last_cs);
   c->cs_tab = (float2*)(base + L.cs_tab);
   c->cs_rows = (int64_t)cfg->max_q_tokens + sv::kTextRows;
   c->part_o = (float*)(base + L.part_o);

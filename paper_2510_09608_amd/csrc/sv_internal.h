@@ -50,9 +50,7 @@ struct StreamState {
   int32_t next_blk = 0;
   int cur = 0;            // which half of the ping-pong store is live
   int next_parity = 0;    // which entry of next_pos[stream][2] is live
-  // Decoded tokens are registered up to kAhead at a time (launch_meta_tokens): of the last ahead_of `ahead` are registered beyond
-  // len, and the newest token of the stream, if it was decoded, has row cs_row of last_cs.
-  int ahead = 0, ahead_of = 0, cs_row = 0;
+  int ahead = 0;          // decoded tokens registered beyond len (launch_meta_tokens: up to kAhead at a time)
   int64_t vis_lo = 0;     // vision ranks present are [vis_lo, n_vis)
   std::vector<std::pair<int64_t, int64_t>> text_iv;  // text ranks present, disjoint half-open intervals
   std::vector<int64_t> layer_len;                    // tokens stored per layer
@@ -95,12 +93,12 @@ struct sv_cache {
   sv::MetaPtrs meta[2];      // device, stream 0; per-stream offset = stream * capacity elements
   int32_t* src;              // device [n_streams][capacity]   gather list of the last eviction
   int32_t* turn;             // device [n_streams][capacity]   re-rotation of the last eviction: 1 + row of dtab, 0: none
-  float2* dtab;              // device [n_streams][capacity][head_dim/2]  cos/sin of position shifts, row = a slot that has it
+  float2* dtab;              // device [n_streams][capacity][head_dim/2]  during an eviction cos/sin of position shifts, row = a slot
+                             // that has it; between evictions cos/sin at the positions of the slots that decode steps registered,
+                             // a row for each of them, so that a captured step finds its own after later registrations
   int32_t* next_pos;         // device [n_streams][2]          scalar position of the next token to register (ping-pong)
   int32_t* n_dev;            // device [n_streams]             registered tokens (the stream's, and those registered ahead)
   double* inv_freq;          // device [head_dim/2]
-  float2* last_cs;           // device [n_streams][kAhead][head_dim/2]  cos/sin at the positions of the decoded tokens that
-                             // were registered together
   float2* cs_tab;            // device [n_streams][cs_rows][head_dim/2]  cos/sin of the tokens of the last
                              // registered run (written when it has at most max_q_tokens tokens)
   int64_t cs_rows;           // max_q_tokens + kTextRows
@@ -123,7 +121,9 @@ struct sv_cache {
   mutable sv::ChunkPlan chunk_plan, store_plan;   // host only; a handle is used by one thread at a time
 
   // cos/sin at the position of the stream's newest token, a decoded one
-  float2* token_cs(int stream) const { return last_cs + ((size_t)stream * sv::kAhead + st[stream].cs_row) * (cfg.head_dim / 2); }
+  float2* token_cs(int stream) const {
+    return dtab + ((size_t)stream * cfg.capacity_tokens + st[stream].len - 1) * (cfg.head_dim / 2);
+  }
   // cos/sin of the pending run's tokens
   float2* run_cs(int stream) const { return cs_tab + ((size_t)stream * cs_rows + st[stream].cs_row0) * (cfg.head_dim / 2); }
   char* kv_ptr(int stream, int half, int layer, int which) const {

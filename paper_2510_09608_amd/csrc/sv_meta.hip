@@ -97,7 +97,8 @@ __global__ void k_meta_append(MetaPtrs m, const int32_t* __restrict__ next_in, i
 // and a gap each: 0.7 of the 3.4 ms that a second of 16 ragged streams took at 4 layers).  What a decoded token's registration
 // writes (arrival id, rank, position, rotary cos/sin) follows from the stream's counts alone, so kAhead steps share one launch: the
 // steps behind the first find their token registered unless the stream was appended to or evicted in between, which starts from
-// the tokens that are really there.  A launch in every step, back to back with the attention, took 5.1 us: 16 ragged
+// the tokens that are really there.  A token's cos/sin have a row by slot: a captured step may hold no registration, and when it
+// is replayed later steps have registered other tokens.  A launch in every step, back to back with the attention, took 5.1 us: 16 ragged
 // streams, 4 layers, 16 tokens 2714 -> 2657 us; one stream, 28 layers, 256 vision and 16 text tokens layer by layer 3811 -> 3770.
 // ---------------------------------------------------------------------------------
 struct TokenRow {
@@ -110,19 +111,17 @@ struct TokenTable {
   TokenRow r[kMaxTokenRows];
 };
 __global__ __launch_bounds__(64) void k_meta_tokens(MetaPtrs m0, MetaPtrs m1, int32_t* __restrict__ next_pos,
-                                                    float2* __restrict__ last_cs, const double* __restrict__ inv_freq,
+                                                    float2* __restrict__ slot_cs, const double* __restrict__ inv_freq,
                                                     int32_t* __restrict__ n_dev, int64_t capacity, int half, int rope3d,
                                                     int rope_none, int f32_data, TokenTable tab) {
   const TokenRow r = tab.r[blockIdx.x];
   const int sid = r.stream >> 2, parity = r.stream & 1, lane = threadIdx.x, j = blockIdx.y, n_ahead = gridDim.y;
   const int next = next_pos[2 * sid + parity];
   const int p = (rope3d ? next : r.slot) + j;   // 1-D: position == slot
-  if (lane < half) {
-    last_cs[((size_t)sid * kAhead + j) * half + lane] = rope_none ? make_float2(1.f, 0.f) : angle_cs(p, inv_freq[lane], f32_data);
-  }
+  const int64_t at = (int64_t)sid * capacity + r.slot + j;
+  if (lane < half) slot_cs[at * half + lane] = rope_none ? make_float2(1.f, 0.f) : angle_cs(p, inv_freq[lane], f32_data);
   if (lane == 0) {
     const bool second = (r.stream & 2) != 0;
-    const int64_t at = (int64_t)sid * capacity + r.slot + j;
     (second ? m1.gid : m0.gid)[at] = r.gid + j;
     (second ? m1.rank : m0.rank)[at] = r.rank + j;
     (second ? m1.type : m0.type)[at] = (uint8_t)SV_TEXT;
@@ -457,7 +456,7 @@ hipError_t launch_meta_tokens(const sv_cache* c, const int32_t* streams, int n_l
       const StreamState& st = c->st[sid];
       tab.r[b] = {st.next_gid, st.n_text, (int32_t)st.len, sid << 2 | st.cur << 1 | st.next_parity};
     }
-    hipLaunchKernelGGL(k_meta_tokens, dim3(nr, n_ahead), dim3(64), 0, s, c->meta[0], c->meta[1], c->next_pos, c->last_cs,
+    hipLaunchKernelGGL(k_meta_tokens, dim3(nr, n_ahead), dim3(64), 0, s, c->meta[0], c->meta[1], c->next_pos, c->dtab,
                        c->inv_freq, c->n_dev, c->cfg.capacity_tokens, c->cfg.head_dim / 2,
                        c->cfg.rope_mode == SV_ROPE_3D ? 1 : 0, c->cfg.rope_mode == SV_ROPE_NONE ? 1 : 0,
                        c->cfg.dtype == SV_DTYPE_F32 ? 1 : 0, tab);

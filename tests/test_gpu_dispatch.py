@@ -952,6 +952,59 @@ def test_decoded_tokens_registered_ahead(dtype, hq, hkv, d, mode, flags):
     check("refused")
 
 
+@pytest.mark.parametrize("dtype,hq,hkv,d,flags", [
+    ("bf16", 4, 2, 128, 0), ("bf16", 4, 4, 64, 0), ("f32", 2, 1, 64, 0), ("bf16", 4, 2, 128, sv.SV_FLAG_GENERIC_KERNELS)])
+@pytest.mark.parametrize("ids", [[0], [1, 0]])
+def test_captured_decode_steps_replayed_after_later_registrations(dtype, hq, hkv, d, flags, ids):
+    """Decode steps (1-D positions) in graphs that hold no registration and that hold two in their middle, replayed again after the
+    steps behind them and with eager work in between: bit for bit what another cache gives that takes the steps one by one."""
+    dt, code = (torch.float32, sv.SV_DTYPE_F32) if dtype == "f32" else (torch.bfloat16, sv.SV_DTYPE_BF16)
+    a, b = (sv.Cache(2, hq, hkv, d, code, sv.SV_ROPE_1D, 1e4, (0, 0, 0), 2, 400, 16, flags=flags) for _ in range(2))
+    g = torch.Generator(device="cuda:0").manual_seed(79)
+    rnd = lambda *shape: torch.randn(*shape, device="cuda:0", generator=g).to(dt)
+    for s in range(2):
+        for layer in range(2):
+            k, v = rnd(300 + s, hkv, d), rnd(300 + s, hkv, d)
+            for c in (a, b):
+                c.append(s, layer, np.zeros(300 + s, np.uint8) if layer == 0 else None, None, k, v)
+    steps, n = 41, len(ids)
+    q, k, v = rnd(steps, 2, n, hq, d), rnd(steps, 2, n, hkv, d), rnd(steps, 2, n, hkv, d)
+    oa, ob = torch.empty_like(q), torch.empty_like(q)
+
+    def run(c, o, t0, t1):
+        for t in range(t0, t1):
+            for layer in range(2):
+                c.decode_step(layer, ids, q[t, layer], k[t, layer], v[t, layer], o[t, layer])
+
+    def captured(t0, t1):
+        torch.cuda.synchronize()
+        graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        with torch.cuda.graph(graph, stream=side):
+            run(a, oa, t0, t1)
+        graph.replay()
+        torch.cuda.synchronize()
+        return graph
+
+    run(b, ob, 0, steps)
+    run(a, oa, 0, 3)
+    graphs = [captured(3, 6)]
+    run(a, oa, 6, 15)
+    graphs.append(captured(15, steps))
+    assert torch.equal(oa, ob)
+    for graph, t0, t1 in ((graphs[0], 3, 6), (graphs[1], 15, steps), (graphs[1], 15, steps), (graphs[0], 3, 6)):
+        print(f"{dtype} {hq}/{hkv} x {d} flags {flags} rows {ids}: steps {t0} to {t1} again", flush=True)
+        oa[t0:t1] = float("nan")
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(oa, ob)
+    for s in ids:
+        assert a.len(s) == b.len(s) == 300 + s + steps
+        for x, y in zip(a.retained(s), b.retained(s)):
+            assert np.array_equal(x, y)
+        for which in range(2):
+            assert all(np.array_equal(a.read_kv(s, layer, which, 0, a.len(s)), b.read_kv(s, layer, which, 0, a.len(s))) for layer in range(2))
+
+
 @pytest.mark.parametrize("hq,hkv,d", [(28, 4, 128), (16, 2, 64), (3, 3, 128), (8, 1, 64)])
 @pytest.mark.parametrize("n_q,n_kv", [(1, 2100), (5, 4200), (37, 4300), (73, 2200), (200, 1100), (300, 700)])
 def test_chunk_merge_of_few_and_of_many_ranges(hq, hkv, d, n_q, n_kv):
