@@ -524,6 +524,31 @@ def test_decode_outputs_shared_out_in_finer_units(dtype, hq, hkv, d, n):
     test_decode_merge_left_to_late_workgroups(dtype, hq, hkv, d, [n])
 
 
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (28, 4, 128), (16, 2, 64), (2, 2, 64), (1, 1, 128)])
+def test_decode_merges_of_up_to_64_key_ranges_and_of_more(hq, hkv, d):
+    """Streams that grow from 64 key ranges to 65 (28 / 4 heads: one tile per wavefront is forced), and 127 and 128 ranges: 32, 16 and
+    8 outputs at a time, by a wavefront each or by all of them, waiting and late."""
+    w = si.Workload("m", 1, hq, hkv, d, "bf16", 2, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, 9971)
+    f64 = lambda x: x.astype(np.float64)
+    lens = [64 * 128 - 1, 126 * 128 + 1, 127 * 128] if hkv < 4 else [64 * 128 - 1]
+    cache = sv.Cache(1, hq, hkv, d, sv.SV_DTYPE_BF16, sv.SV_ROPE_NONE, 1e4, (0, 0, 0), len(lens), max(lens) + 8, 16)
+    q, k, v = w.qkv(0, np.arange(max(lens) + 2))
+    for b, n in enumerate(lens):
+        cache.append(b, 0, np.zeros(n, np.uint8), None, gu.dev(k[:n], w), gu.dev(v[:n], w))
+        for m in (n + 1, n + 2):
+            print(f"{hq}/{hkv} x {d} {m} tokens", flush=True)
+            x, out = slice(m - 1, m), []
+            for option in (1 if hkv == 4 else 0, sv.SV_MERGE_ONE_LOOK + (1 if hkv == 4 else 0)):
+                cache.set_option(sv.SV_OPT_DECODE_TILES_PER_WAVE, option)
+                out.append(torch.full((1, hq, d), float("nan"), device="cuda:0", dtype=torch.bfloat16))
+                if option < sv.SV_MERGE_ONE_LOOK:
+                    cache.decode_step(0, [b], gu.dev(q[x], w), gu.dev(k[x], w), gu.dev(v[x], w), out[-1])
+                else:
+                    cache.attn_decode(0, [b], gu.dev(q[x], w), out[-1])
+            ref = orc.gqa_attention(f64(q[x]), f64(k[:m]), f64(v[:m]), np.array([m - 1]), True)
+            assert gu.max_err(gu.host(out[0]), ref) <= gu.TOL["bf16"] and torch.equal(out[0], out[1])
+
+
 @pytest.mark.parametrize("hq,hkv,d,n", [
     (12, 12, 128, 2688), (12, 12, 128, 2689), (12, 12, 128, 3040), (12, 12, 128, 3041), (12, 12, 128, 3700), (12, 12, 128, 4300),
     (12, 12, 128, 4865), (16, 4, 64, 8225), (8, 1, 128, 8193), (8, 1, 128, 10300)])
