@@ -165,8 +165,18 @@ __device__ __forceinline__ void rope_rows(int bx, T* __restrict__ x, const int4*
   *(decltype(hi.raw)*)(p + D / 2 + t * G::EPV) = hi.raw;
 }
 
-// The same as a launch of its own.  A thread takes its place of HG heads of a token: position, cos/sin and what is divided are worked
-// out once for them, below the rows' loads.  With a head per thread, and the token from a 64-bit division, the launch was bound by
+// The same as a launch of its own: a head per thread, rows as they lie (fp32 up to 600 workgroups or with one head, see rope_apply_t).
+// grid: ceil(n * n_heads / ROWS)
+template <typename T, int D>
+__global__ __launch_bounds__(256) void k_rope_rows_flat(T* __restrict__ x, const int4* __restrict__ pos4,
+                                                        const double* __restrict__ inv_freq, int64_t slot0, int n,
+                                                        int n_heads, int rope_mode, int s0, int s01,
+                                                        const float2* __restrict__ cs_tab) {
+  rope_rows<T, D>(blockIdx.x, x, pos4, inv_freq, slot0, n, n_heads, rope_mode, s0, s01, cs_tab);
+}
+
+// A thread takes its place of HG heads of a token: position, cos/sin and what is divided are worked out once for them, below the
+// rows' loads.  With a head per thread, and the token from a 64-bit division, the launch was bound by
 // that: 5376 tokens of 28 heads (77 MB) 17.2 us, with 4 heads 13.0 (5.9 TB/s).
 // grid: ceil(n / ROWS) * ceil(n_heads / HG), the heads' shares side by side.  cs_tab: of the run that starts at slot0, or NULL.
 template <typename T, int D, int HG>
@@ -544,17 +554,22 @@ hipError_t rope_apply_t(const sv_cache* c, int stream, int64_t slot0, int n, voi
   const int heads[2] = {c->cfg.n_q_heads, c->cfg.n_kv_heads};
   for (int a = 0; a < 2; ++a) {
     if (!ptrs[a]) continue;
-    auto launch = [&](auto kernel, int hg) {
-      const int64_t groups = (int64_t)((n + G::ROWS - 1) / G::ROWS) * ((heads[a] + hg - 1) / hg);
-      hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(256), 0, s, (T*)ptrs[a], c->meta[cur].pos4 + off, c->inv_freq, slot0, n,
-                         heads[a], c->cfg.rope_mode, s0, s01, run_table(c, stream, slot0, n));
+    const int h = heads[a];
+    auto launch = [&](auto kernel, int64_t workgroups) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)workgroups), dim3(256), 0, s, (T*)ptrs[a], c->meta[cur].pos4 + off, c->inv_freq, slot0, n,
+                         h, c->cfg.rope_mode, s0, s01, run_table(c, stream, slot0, n));
     };
+    const int64_t blocks = (n + G::ROWS - 1) / G::ROWS, full = (int64_t)n * h / G::ROWS;
     // The more heads per thread that leave some 400 workgroups (us, 1, 2 and 4 heads: 2000 x 28 8.2, 7.75 and 7.5, 5000 x 8 6.3, 6.25 and
-    // 6.6, 3000 x 12 6.1, 6.0 and 6.1, 700 x 28 4.4, 4.2 and 4.2).
-    const int64_t full = (int64_t)n * heads[a] / G::ROWS;
-    if (full >= 1600) launch(k_rope_rows<T, D, 4>, 4);
-    else if (full >= 600) launch(k_rope_rows<T, D, 2>, 2);
-    else launch(k_rope_rows<T, D, 1>, 1);
+    // 6.6, 3000 x 12 6.1, 6.0 and 6.1, 700 x 28 4.4, 4.2 and 4.2), but with at most a quarter of a token's places empty, whose threads
+    // load a row that is there again (1, 2 and 4 heads: 131000 tokens of one head of 128 15.1, 15.3 and 16.7, 95000 of two of
+    // 64 11.0, 8.7 and 9.3, 26000 of five of 128 14.1, 12.3 and 14.6, 29000 of three 10.7, 9.8 and 8.0, 22000 of six 14.6, 11.3 and 11.5).
+    // fp32 with one head each: rows as they lie are the faster way (28 heads of 128, 126 tokens 3.20 and 3.32, 255 3.85 and 3.98; bf16 is
+    // 1 % slower so).
+    if (full >= 1600 && 3 * ((h + 3) / 4) <= h) launch(k_rope_rows<T, D, 4>, blocks * ((h + 3) / 4));
+    else if (full >= 600 && h >= 2) launch(k_rope_rows<T, D, 2>, blocks * ((h + 1) / 2));
+    else if constexpr (sizeof(T) == 4) launch(k_rope_rows_flat<T, D>, ((int64_t)n * h + G::ROWS - 1) / G::ROWS);
+    else launch(k_rope_rows<T, D, 1>, blocks * h);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -1051,8 +1051,11 @@ def test_chunk_merge_of_few_and_of_many_ranges(hq, hkv, d, n_q, n_kv):
             assert gu.max_err(gu.host(od), ref) <= gu.TOL["bf16"]
 
 
+# (28 and 30 heads of 3500 tokens, 7 of 15000 and 3 of 34200 take four heads to a thread in every layout, 5 of 21000 and 2 of 51300 two,
+# 1 of 102500 one)
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
-@pytest.mark.parametrize("hq,n", [(28, 1843), (30, 700), (7, 2750), (1, 33)])
+@pytest.mark.parametrize("hq,n", [(28, 1843), (30, 700), (7, 2750), (1, 33), (28, 3700), (30, 3501), (7, 15001), (3, 34201), (5, 21001),
+                                  (2, 51301), (1, 102501)])
 def test_rotation_of_long_runs(dtype, d, hq, n):
     """Rows rotated one, two and four heads to a thread, with and without the run's table, heads that fill the last share and that do
     not: bit for bit what pieces of 31 tokens give, whose heads go one by one."""
