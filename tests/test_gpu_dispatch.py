@@ -1033,8 +1033,9 @@ def test_captured_decode_steps_replayed_after_later_registrations(dtype, hq, hkv
 @pytest.mark.parametrize("hq,hkv,d", [(28, 4, 128), (16, 2, 64), (3, 3, 128), (8, 1, 64)])
 @pytest.mark.parametrize("n_q,n_kv", [(1, 2100), (5, 4200), (37, 4300), (73, 2200), (200, 1100), (300, 700)])
 def test_chunk_merge_of_few_and_of_many_ranges(hq, hkv, d, n_q, n_kv):
-    """Chunks in 2 to 64 key ranges, as whole numbers per group of lanes and not, one, two and four groups to a row, heads that fill a
-    workgroup's groups and that do not, and causal rows that see only some of the ranges, against the oracle."""
+    """Chunks in 2 to 34 key ranges of several tiles (as many as the keys and the scratch memory allow of those asked for), one, two and
+    four groups of lanes to a row, heads that fill a workgroup's groups and that do not, and causal rows that see only some of the ranges,
+    against the oracle."""
     w = si.Workload("m", 1, hq, hkv, d, "bf16", 2, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, 771)
     cache = sv.Cache(1, hq, hkv, d, sv.SV_DTYPE_BF16, sv.SV_ROPE_NONE, 1e4, (0, 0, 0), 1, n_kv, n_q)
     q, k, v = w.qkv(0, np.arange(n_kv))
@@ -1049,6 +1050,34 @@ def test_chunk_merge_of_few_and_of_many_ranges(hq, hkv, d, n_q, n_kv):
             od = torch.full_like(qd, float("nan"))
             cache.attn_chunk(0, 0, qd, od, causal)
             assert gu.max_err(gu.host(od), ref) <= gu.TOL["bf16"]
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(28, 4, 128), (16, 2, 64), (3, 3, 128), (8, 1, 64)])
+def test_chunk_merge_of_every_number_of_ranges_per_lane(hq, hkv, d):
+    """A stream that grows tile by tile to 64 key ranges of one tile each: every number of ranges that a lane of the merge takes with one,
+    two and four groups of lanes to a row, with and without one less for the last groups, full and with a last tile of one key, which
+    not all rows see, against the oracle."""
+    w = si.Workload("m", 1, hq, hkv, d, "bf16", 2, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, 773)
+    cache = sv.Cache(1, hq, hkv, d, sv.SV_DTYPE_BF16, sv.SV_ROPE_NONE, 1e4, (0, 0, 0), 1, 64 * 64, 37)
+    cache.set_option(sv.SV_OPT_CHUNK_SPLITS, 64)
+    q, k, v = w.qkv(0, np.arange(64 * 64))
+    f64 = lambda x: x.astype(np.float64)
+    ranges = list(range(2, 25)) + [n for n in range(25, 65) if n % 4 in (0, 1)]
+    seen, had = set(), 0
+    for n in ranges:
+        groups = 1 if n <= 12 else 2 if n <= 24 else 4
+        seen.add((groups, -(-n // groups), n % groups == 0))
+        for n_kv, n_q in ((64 * n - 63, 5), (64 * n, 5 if n % 5 else 37)):
+            print(f"{hq}/{hkv} x {d} {n} ranges n_kv={n_kv} n_q={n_q}", flush=True)
+            cache.append(0, 0, np.zeros(n_kv - had, np.uint8), None, gu.dev(k[had:n_kv], w), gu.dev(v[had:n_kv], w))
+            had = n_kv
+            x = q[n_kv - n_q:n_kv]
+            ref = orc.gqa_attention(f64(x), f64(k[:n_kv]), f64(v[:n_kv]), np.arange(n_kv - n_q, n_kv), True)
+            od = torch.full((n_q, hq, d), float("nan"), device="cuda:0", dtype=torch.bfloat16)
+            cache.attn_chunk(0, 0, gu.dev(x, w), od, True)
+            assert gu.max_err(gu.host(od), ref) <= gu.TOL["bf16"]
+    assert seen == {(1, i, True) for i in range(2, 13)} | {(2, i, e) for i in range(7, 13) for e in (True, False)} | {
+        (4, i, e) for i in range(7, 17) for e in (True, False)}
 
 
 # (28 and 30 heads of 3500 tokens, 7 of 15000 and 3 of 34200 take four heads to a thread in every layout, 5 of 21000 and 2 of 51300 two,
