@@ -150,7 +150,8 @@ void note_text_registered(sv::StreamState& st, int n, bool cs_tab_valid, bool wi
 }
 
 // The next decoded token of each of n_list distinct streams, which have room for it: registered by a launch where an earlier one
-// has not done so already.
+// has not done so already.  A stream that is nearly full shortens the launch for the others to the tokens it has room for, once: they
+// are all it will decode before it is cut.
 hipError_t register_tokens(sv_cache* c, const int32_t* streams, int n_list, hipStream_t s) {
   constexpr int kGroup = 64;
   for (int b0 = 0; b0 < n_list; b0 += kGroup) {

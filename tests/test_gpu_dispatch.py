@@ -1104,7 +1104,7 @@ def test_rotation_of_long_runs(dtype, d, hq, n):
 
 
 @pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (2, 1, 64), (9, 3, 64), (5, 5, 128)])
-@pytest.mark.parametrize("n_q,n_kv", [(1, 1100), (9, 2100), (70, 2200), (200, 300)])
+@pytest.mark.parametrize("n_q,n_kv", [(1, 1100), (9, 2100), (70, 2200), (200, 300), (9, 2048), (40, 2019)])
 def test_fp32_chunk_merge_of_few_and_of_many_ranges(hq, hkv, d, n_q, n_kv):
     """fp32 chunks in 2 to 64 key ranges, one, two and four groups of lanes to a row, whole passes and not, heads that fill a workgroup
     and that do not, causal rows that see only some of the ranges, against the oracle."""
