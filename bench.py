@@ -30,8 +30,8 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 MFMA, published
 MEASURED_TRAFFIC = {
     # attn_chunk = k_attn_chunk_pipe (which stores the chunk's K/V itself at this workload) + k_chunk_combine; decode_sweep =
     # k_decode_one (key ranges merged in the same launch); evict = k_evict_scan + k_compact (reads + writes, scaled counters)
-    "qwen7b_256v_28L": {"attn_chunk": (29.5e6 + 18.1e6) + (18.0e6 + 1.8e6),
-                        "decode_sweep": 12.69e6 + 1.52e6,
+    "qwen7b_256v_28L": {"attn_chunk": (29.6e6 + 20.0e6) + (17.7e6 + 1.8e6),
+                        "decode_sweep": 12.66e6 + 1.53e6,
                         "evict": (264.5e6 + 264.2e6) + (0.5e6 + 0.5e6)},
 }
 
