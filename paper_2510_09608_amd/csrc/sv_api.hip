@@ -311,6 +311,7 @@ int sv_cache_create(const sv_config* cfg, void* dev_arena, size_t arena_bytes, v
   if (e == hipSuccess && c->v_blocked)
     e = hipMemsetAsync(c->kv_base, 0, (size_t)cfg->n_streams * c->stream_kv_stride, s);
   if (e == hipSuccess && c->use_mfma) e = sv::attn_chunk_mfma_init();
+  if (e == hipSuccess && c->f32_mfma) e = sv::attn_chunk_f32_init();
   if (e == hipSuccess && c->use_mfma) {   // device address of sv_attn_decode_static's scratch array, once per device
     void* p = nullptr;
     e = sv::decode_static_scratch(&p);

@@ -72,12 +72,14 @@ struct StreamState {
 };
 
 // Key ranges of the last chunk-prefill launch and the counts they were chosen for: the layers of a chunk ask in turn.
+enum class F32Chunk : uint8_t { plain, few, terms };   // kernels of fp32 chunk prefill
+
 struct ChunkPlan {
   int n_q = 0, n_kv = 0;
   bool causal = false;
   int forced = 0, n_splits = 0, keys_per_split = 0;
   double us = 0;     // estimate
-  bool few = false;  // fp32: the kernel for few rows
+  F32Chunk f32 = F32Chunk::plain;
 };
 
 }  // namespace sv
@@ -212,8 +214,9 @@ hipError_t launch_attn_chunk_f32(const sv_cache* c, int stream, int layer, const
                                  hipStream_t s, const void* k_new = nullptr, const void* v_new = nullptr);
 bool attn_chunk_f32_stores_tokens(const sv_cache* c, int stream, int n_q);
 
-// Once per process and device, before the first chunk-prefill launch: the kernel's LDS size has to be asked for.
+// Once per process and device, before the first chunk-prefill launch: the kernels' LDS size has to be asked for.
 hipError_t attn_chunk_mfma_init();
+hipError_t attn_chunk_f32_init();
 // Store n new tokens of one layer (K rows rotated; V as the cache keeps it: transposed into its blocks, or row-major)
 // and, if q is not NULL, rotate their Q rows in place, all in one launch.  Cos/sin come from c->cs_tab when the
 // stream's table is valid for this run.

@@ -125,3 +125,39 @@ def test_fp32_infinite_value_stays_infinite(hq, hkv, d):
     for o in outs:
         x = gu.host(o)
         assert (np.isposinf(x) == want).all() and np.isfinite(x[:, ~want]).all()
+
+
+@pytest.mark.parametrize("hq,hkv,d,n_kv,n_q,causal,splits", [
+    (8, 2, 128, 403, 403, True, 1),     # row tiles that see 1 to 13 tiles of keys: halves with a tile more than the other, or none
+    (8, 2, 128, 416, 33, False, 1), (8, 2, 128, 1031, 65, True, 2), (6, 6, 128, 700, 129, True, 1), (28, 4, 128, 1500, 200, True, 3),
+    (2, 1, 64, 320, 320, True, 1), (8, 8, 64, 353, 161, False, 1), (14, 2, 64, 2000, 90, True, 4)])
+def test_fp32_chunk_from_bf16_terms_is_as_exact_as_its_sums(hq, hkv, d, n_kv, n_q, causal, splits):
+    """Launches of four and more tiles of 32 keys per range, whose products are made of bf16 terms: the bound of the fp32
+    instructions (what the six products leave out and the matrix cores' rounding are in what is measured below it)."""
+    assert chunk_error("f32", hq, hkv, d, n_kv, n_q, causal, splits)[0] <= 3.6 * U
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (8, 8, 64)])
+@pytest.mark.parametrize("q_exp,k_exp,v_exp,ignored", [(70, -70, 0, False), (-110, 110, 0, False), (0, 0, -115, False), (0, 0, 100, False), (0, 0, 0, True)])
+def test_fp32_chunk_of_numbers_that_terms_do_not_hold(hq, hkv, d, q_exp, k_exp, v_exp, ignored):
+    """Queries, keys and values scaled by powers of two whose bf16 terms would lose bits, and a key whose scores are minus
+    infinity: results as exact as ever."""
+    print(f"terms {hq}/{hkv} x {d}: 2^{q_exp} 2^{k_exp} 2^{v_exp} ignored={ignored}", flush=True)
+    n_kv, n_q = 330, 140
+    w = si.Workload("t", 1, hq, hkv, d, "f32", 2, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, 9991)
+    cache = sv.Cache(1, hq, hkv, d, sv.SV_DTYPE_F32, sv.SV_ROPE_NONE, 1e4, (0, 0, 0), 1, n_kv + 8, n_q)
+    q, k, v = (x.copy() for x in w.qkv(0, np.arange(n_kv)))
+    q = q[:n_q]
+    if ignored:
+        q[:, :, 3] = np.abs(q[:, :, 3]) + 0.5
+        k[77, :, 3] = -np.inf
+    q, k, v = q * np.float32(2.0 ** q_exp), k * np.float32(2.0 ** k_exp), v * np.float32(2.0 ** v_exp)
+    cache.append(0, 0, np.zeros(n_kv, np.uint8), None, gu.dev(k, w), gu.dev(v, w))
+    cache.set_option(sv.SV_OPT_CHUNK_SPLITS, 1)
+    o = torch.empty(n_q, hq, d, device="cuda:0")
+    cache.attn_chunk(0, 0, gu.dev(q, w), o, False)
+    if ignored:   # (the same with that key left out)
+        k, v = np.delete(k, 77, 0), np.delete(v, 77, 0)
+    ref = orc.gqa_attention(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), np.full(n_q, len(k) - 1), True)
+    s = 2.0 ** -v_exp
+    assert rms_error(torch.from_numpy(gu.host(o).astype(np.float64) * s), ref * s) <= 3.6 * U
