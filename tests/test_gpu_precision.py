@@ -53,9 +53,10 @@ def test_fp32_chunk_is_as_exact_as_its_sums(hq, hkv, d, n_kv, n_q, causal):
     assert chunk_error("f32", hq, hkv, d, n_kv, n_q, causal)[0] <= 3.6 * U
 
 
-def decode_error(dtype, hq, hkv, d, lens, steps=12):
-    print(f"decode {dtype} {hq}/{hkv} x {d}: {lens} keys", flush=True)
+def decode_error(dtype, hq, hkv, d, lens, steps=12, tiles=0):
+    print(f"decode {dtype} {hq}/{hkv} x {d}: {lens} keys, {tiles} tiles", flush=True)
     cache, w, k, v = cache_of(dtype, hq, hkv, d, lens, 16, 9100 + sum(lens))
+    cache.set_option(sv.SV_OPT_DECODE_TILES_PER_WAVE, tiles)
     q = w.qkv(0, np.arange(60000, 60000 + steps * len(lens)))[0].reshape(steps, len(lens), hq, d)
     o = torch.stack([gu.dev(x, w) for x in q])
     for i in range(steps):
@@ -72,6 +73,15 @@ def decode_error(dtype, hq, hkv, d, lens, steps=12):
 def test_fp32_decode_is_as_exact_as_its_sums(hq, hkv, d, lens):
     """Decode of one stream (key ranges merged in the launch) and of several (merged by a launch of its own)."""
     assert decode_error("f32", hq, hkv, d, lens)[0] <= 3.6 * U
+
+
+@pytest.mark.parametrize("tiles", [0, 3])
+@pytest.mark.parametrize("hq,hkv,d", [(2, 2, 128), (4, 2, 128), (3, 1, 128), (8, 2, 128), (8, 8, 64), (2, 1, 64), (6, 2, 64), (16, 4, 64)])
+def test_fp32_decode_of_up_to_four_heads_per_kv_head(hq, hkv, d, tiles):
+    """The 4 x 4 matrix instructions: the first and last key of a tile, wavefronts with one tile, three or none, one stream and
+    several (0: the number of tiles a wavefront is given by itself)."""
+    for lens in ([1], [15], [16], [17], [65], [129], [407], [33, 200, 1, 64]):
+        assert decode_error("f32", hq, hkv, d, lens, steps=4, tiles=tiles)[0] <= 3.6 * U
 
 
 def rounded_to_bf16(ref):
