@@ -1,4 +1,4 @@
-// Softmax arithmetic of the fp32 attention kernels, shared by chunk prefill and decode.  What an fp32 caller gets is as
+// Softmax arithmetic of the fp32 attention kernels, shared by chunk prefill and decode, and sums over lane groups.  What an fp32 caller gets is as
 // close to the exact result as sums of 32 bits allow: exponents are formed in two floats, sums of products run in short
 // chains that meet pairwise (in the kernels), quotients are rounded once.
 #pragma once
@@ -42,6 +42,29 @@ template <typename V>
 __device__ __forceinline__ V rest_of(const V& a, const V& b, const V& sum) {
   const V b2 = sum - a;
   return (a - (sum - b2)) + (b - b2);
+}
+
+// max / sum over the four lane groups l, l ^ 16, l ^ 32, l ^ 48: two row swaps on the vector ALU (through LDS, as
+// ds_bpermute, each step is a round trip of some 100 cycles)
+__device__ __forceinline__ void swap16(float x, float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  a = __uint_as_float(r[0]), b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap32(float x, float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  a = __uint_as_float(r[0]), b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float groups_max(float x) {
+  float a, b;
+  swap16(x, a, b);
+  swap32(fmaxf(a, b), a, b);
+  return fmaxf(a, b);
+}
+__device__ __forceinline__ float groups_sum(float x) {
+  float a, b;
+  swap16(x, a, b);
+  swap32(a + b, a, b);
+  return a + b;
 }
 
 // A running sum in two floats: what an addition rounds off goes into the second one.
