@@ -59,7 +59,8 @@ __device__ __forceinline__ void dma16x2(const void* base, uint32_t lane_off, uin
 // Chunk attention with its merge, 256 queries of 28 / 4 heads, on 1376 keys 21.1 -> 19.9 us, on 5376 30.7 -> 29.7 (its last
 // partial result was stored after 25.4 us, the merge began after 28.4); decode, 28 / 4 heads, 5392 tokens, 6.10 -> 6.00.
 // Not used where it gains nothing: the moves of whole caches (76 us at head_dim 128 either way; 12 layers of 64 11.6 and 17), the
-// storing of new tokens, fp32 chunk attention (256 on 5392, 4 layers and their decode, 788 us, with it 793).
+// storing of new tokens, fp32 chunk attention by fp32 instructions (256 on 5392, 4 layers and their decode, 788 us, with it 793), merges of
+// fp32 chunks.
 // (16 bytes as assembly, which has no builtin; the s_nop keeps the compiler, which does not know of the store, from overwriting its
 // registers while they are read: a vector instruction that does so has to stay two wait states behind a store of more than 8 bytes.)
 template <typename V>
