@@ -109,7 +109,11 @@ SV_API int sv_cache_destroy(sv_cache* c);
 /*
  * sv_cache_set_option -- per-handle launch overrides; implements no passage of the paper.  Every option
  * defaults to 0 = "let the library choose" (what all measurements use); a positive value forces
- *   SV_OPT_CHUNK_SPLITS           the number of key ranges of sv_attn_chunk's matrix-core kernel,
+ *   SV_OPT_CHUNK_SPLITS           the number of key ranges of sv_attn_chunk's matrix-core kernel;
+ *                                 with SV_CHUNK_F32_PLAIN or SV_CHUNK_F32_TERMS added (a test seam) the chunks of
+ *                                 fp32 caches, whatever their size, go through the kernel of fp32 instructions that
+ *                                 has 32 rows to a wavefront, or through the one of bf16 terms, in that number of
+ *                                 ranges (0: as many as that kernel is expected to need),
  *   SV_OPT_DECODE_TILES_PER_WAVE  the 32-key tiles each wavefront of the decode kernel takes (1..16);
  *                                 with SV_MERGE_ONE_LOOK added (a test seam, results unchanged) a workgroup of the
  *                                 decode kernels that does not find the other key ranges' results at its first look
@@ -128,7 +132,9 @@ enum {
   SV_OPT_DECODE_SPLITS = 2,
   SV_OPT_CHUNK_STORE = 3,
   SV_OPT_COUNT_ = 4,
-  SV_MERGE_ONE_LOOK = 1 << 16
+  SV_MERGE_ONE_LOOK = 1 << 16,
+  SV_CHUNK_F32_PLAIN = 1 << 28,
+  SV_CHUNK_F32_TERMS = 1 << 29
 };
 SV_API int sv_cache_set_option(sv_cache* c, int option, int value);
 

@@ -20,6 +20,7 @@ SV_WINDOW_INF = -1
 SV_FLAG_GENERIC_KERNELS, SV_FLAG_HOST_LOGIC_ONLY = 1, 2
 SV_OPT_CHUNK_SPLITS, SV_OPT_DECODE_TILES_PER_WAVE, SV_OPT_DECODE_SPLITS, SV_OPT_CHUNK_STORE = 0, 1, 2, 3
 SV_MERGE_ONE_LOOK = 1 << 16
+SV_CHUNK_F32_PLAIN, SV_CHUNK_F32_TERMS = 1 << 28, 1 << 29
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 

@@ -10,6 +10,7 @@ from oracle import sv_step
 from tests import gpu_util as gu
 
 pytestmark = pytest.mark.gpu
+PLAIN, TERMS = sv.SV_CHUNK_F32_PLAIN, sv.SV_CHUNK_F32_TERMS
 
 
 def attn_case(dtype, hq, hkv, d, n_kv, n_q, causal, seed, splits=0):
@@ -388,7 +389,8 @@ def test_fp32_decode_of_one_long_stream():
 @pytest.mark.parametrize("n_q", [200, 5])
 def test_wide_score_range_of_every_matrix_core_layout(dtype, hq, hkv, d, n_q):
     """Row maxima that jump by tens to hundreds of binary orders between key tiles, as in test_attn_chunk_wide_score_range:
-    chunk prefill (with 5 queries in fp32 the kernel for few rows) and decode of one and of two rows.
+    chunk prefill (with 5 queries in fp32 the kernel for few rows; in fp32 also the other two kernels, asked for) and decode of one and
+    of two rows.
 
     fp32: a score s is off by up to 4 x 1.6 times 2^-24 of its size (see test_gpu_precision) and its weight by as much of
     itself.  What that does to a row's output: the largest weight p multiplies a value within (1 - p) x 9 of the output (values
@@ -426,7 +428,7 @@ def test_wide_score_range_of_every_matrix_core_layout(dtype, hq, hkv, d, n_q):
         cache.append(s, 0, np.zeros(n_kv, np.uint8), None, gu.dev(k, w), gu.dev(v, w))
     qd = gu.dev(q, w)
     for causal in (True, False):
-        for splits in (0, 1, 4):
+        for splits in (0, 1, 4) + ((1 | PLAIN, 4 | PLAIN, 1 | TERMS, 4 | TERMS) if dtype == "f32" else ()):
             print(f"wide scores {dtype} {hq}/{hkv} x {d} n_q={n_q} causal={causal} splits={splits}", flush=True)
             cache.set_option(sv.SV_OPT_CHUNK_SPLITS, splits)
             od = torch.full_like(qd, float("nan"))
@@ -1116,7 +1118,7 @@ def test_fp32_chunk_merge_of_few_and_of_many_ranges(hq, hkv, d, n_q, n_kv):
     qd = gu.dev(q, w)
     for causal in (True, False):
         ref = orc.gqa_attention(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), np.arange(n_kv - n_q, n_kv), causal)
-        for splits in (0, 2, 7, 8, 9, 15, 16, 17, 31, 34, 64):
+        for splits in (0, 2, 7, 8, 9, 15, 16, 17, 31, 34, 64, 1 | PLAIN, 3 | PLAIN, 17 | PLAIN, 1 | TERMS, 3 | TERMS, 17 | TERMS, 64 | TERMS):
             print(f"f32 {hq}/{hkv} x {d} n_q={n_q} n_kv={n_kv} causal={causal} splits={splits}", flush=True)
             cache.set_option(sv.SV_OPT_CHUNK_SPLITS, splits)
             od = torch.full_like(qd, float("nan"))

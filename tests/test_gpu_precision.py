@@ -16,6 +16,7 @@ from tests import gpu_util as gu
 pytestmark = pytest.mark.gpu
 
 U = 2.0 ** -24
+PLAIN, TERMS = sv.SV_CHUNK_F32_PLAIN, sv.SV_CHUNK_F32_TERMS
 
 
 def cache_of(dtype, hq, hkv, d, lens, max_q, seed):
@@ -33,7 +34,11 @@ def rms_error(o, ref):
     return float(np.sqrt(np.mean((gu.host(o) - ref) ** 2) / np.mean(ref ** 2)))
 
 
-def chunk_error(dtype, hq, hkv, d, n_kv, n_q, causal, splits=0):
+def chunk_error(*case):
+    return chunk_case(*case)[:2]
+
+
+def chunk_case(dtype, hq, hkv, d, n_kv, n_q, causal, splits=0):
     print(f"chunk {dtype} {hq}/{hkv} x {d}: {n_q} queries, {n_kv} keys, {splits} ranges", flush=True)
     cache, w, k, v = cache_of(dtype, hq, hkv, d, [n_kv], n_q, 9000 + n_kv)
     cache.set_option(sv.SV_OPT_CHUNK_SPLITS, splits)
@@ -42,15 +47,24 @@ def chunk_error(dtype, hq, hkv, d, n_kv, n_q, causal, splits=0):
     o = torch.empty_like(qd)
     cache.attn_chunk(0, 0, qd, o, causal)
     ref = orc.gqa_attention(q.astype(np.float64), k, v, np.arange(n_kv - n_q, n_kv), causal)
-    return rms_error(o, ref), ref
+    return rms_error(o, ref), ref, o
 
 
 @pytest.mark.parametrize("hq,hkv,d,n_kv,n_q,causal", [
     (28, 4, 128, 400, 64, True), (8, 2, 128, 72, 16, True), (8, 2, 128, 2600, 300, True), (28, 4, 128, 1500, 9, False),
     (2, 1, 64, 400, 16, True), (8, 8, 64, 400, 130, True), (8, 8, 64, 2600, 500, True)])
 def test_fp32_chunk_is_as_exact_as_its_sums(hq, hkv, d, n_kv, n_q, causal):
-    """Chunk prefill of both fp32 kernels and their merge."""
+    """Chunk prefill as the library chooses kernel and key ranges, and their merge."""
     assert chunk_error("f32", hq, hkv, d, n_kv, n_q, causal)[0] <= 3.6 * U
+
+
+@pytest.mark.parametrize("hq,hkv,d,n_kv,n_q,causal,splits", [
+    (28, 4, 128, 586, 586, True, 0), (32, 8, 128, 587, 287, True, 0), (8, 8, 128, 821, 521, True, 0), (8, 2, 128, 1156, 456, True, 0),
+    (8, 2, 128, 2600, 300, True, 1), (28, 4, 128, 1500, 200, False, 2), (14, 2, 64, 2000, 90, True, 2), (8, 8, 64, 2600, 500, True, 4)])
+def test_fp32_chunk_by_fp32_instructions_is_as_exact_as_its_sums(hq, hkv, d, n_kv, n_q, causal, splits):
+    """Ranges of 4 to 82 tiles of 32 keys through the kernel that has 32 rows to a wavefront: tiles that take turns in LDS, sums
+    rescaled on the way."""
+    assert chunk_error("f32", hq, hkv, d, n_kv, n_q, causal, splits | PLAIN)[0] <= 3.6 * U
 
 
 def decode_error(dtype, hq, hkv, d, lens, steps=12, tiles=0):
@@ -122,7 +136,7 @@ def test_fp32_infinite_value_stays_infinite(hq, hkv, d):
     want[:hq // hkv, 5] = True
     outs = []
     for n_q in (100, 3):
-        for splits in (1, 3):
+        for splits in (1, 3, 1 | PLAIN, 3 | PLAIN, 1 | TERMS, 3 | TERMS):
             print(f"infinite value {hq}/{hkv} x {d} n_q={n_q} splits={splits}", flush=True)
             cache.set_option(sv.SV_OPT_CHUNK_SPLITS, splits)
             o = torch.empty(n_q, hq, d, device="cuda:0")
@@ -142,16 +156,21 @@ def test_fp32_infinite_value_stays_infinite(hq, hkv, d):
     (8, 2, 128, 416, 33, False, 1), (8, 2, 128, 1031, 65, True, 2), (6, 6, 128, 700, 129, True, 1), (28, 4, 128, 1500, 200, True, 3),
     (2, 1, 64, 320, 320, True, 1), (8, 8, 64, 353, 161, False, 1), (14, 2, 64, 2000, 90, True, 4)])
 def test_fp32_chunk_from_bf16_terms_is_as_exact_as_its_sums(hq, hkv, d, n_kv, n_q, causal, splits):
-    """Launches of four and more tiles of 32 keys per range, whose products are made of bf16 terms: the bound of the fp32
-    instructions (what the six products leave out and the matrix cores' rounding are in what is measured below it)."""
-    assert chunk_error("f32", hq, hkv, d, n_kv, n_q, causal, splits)[0] <= 3.6 * U
+    """The kernel whose products are made of bf16 terms, on four and more tiles of 32 keys per range: the bound of the fp32
+    instructions (what the six products leave out and the matrix cores' rounding are in what is measured below it), and other
+    bits than theirs."""
+    err, _, o = chunk_case("f32", hq, hkv, d, n_kv, n_q, causal, splits | TERMS)
+    assert err <= 3.6 * U
+    assert not torch.equal(chunk_case("f32", hq, hkv, d, n_kv, n_q, causal, splits | PLAIN)[2], o)
 
 
 @pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (8, 8, 64)])
-@pytest.mark.parametrize("q_exp,k_exp,v_exp,ignored", [(70, -70, 0, False), (-110, 110, 0, False), (0, 0, -115, False), (0, 0, 100, False), (0, 0, 0, True)])
+@pytest.mark.parametrize("q_exp,k_exp,v_exp,ignored", [
+    (70, -70, 0, False), (115, -115, 0, False), (-110, 110, 0, False), (-118, 118, 0, False), (0, 0, -115, False), (0, 0, 100, False), (0, 0, 0, True)])
 def test_fp32_chunk_of_numbers_that_terms_do_not_hold(hq, hkv, d, q_exp, k_exp, v_exp, ignored):
-    """Queries, keys and values scaled by powers of two whose bf16 terms would lose bits, and a key whose scores are minus
-    infinity: results as exact as ever."""
+    """Queries, keys and values scaled by powers of two, at which bf16 terms still hold them (70, -110, 100) and would lose bits
+    (115, -118, -115: 17 to 140 times 2^-24 with three terms, as computed in 64 bits), and a key whose scores are minus infinity:
+    results as exact as ever."""
     print(f"terms {hq}/{hkv} x {d}: 2^{q_exp} 2^{k_exp} 2^{v_exp} ignored={ignored}", flush=True)
     n_kv, n_q = 330, 140
     w = si.Workload("t", 1, hq, hkv, d, "f32", 2, 1e4, (0, 0, 0), 0, 0, 0, 0, 0, 0, None, 0, 9991)
@@ -163,7 +182,7 @@ def test_fp32_chunk_of_numbers_that_terms_do_not_hold(hq, hkv, d, q_exp, k_exp, 
         k[77, :, 3] = -np.inf
     q, k, v = q * np.float32(2.0 ** q_exp), k * np.float32(2.0 ** k_exp), v * np.float32(2.0 ** v_exp)
     cache.append(0, 0, np.zeros(n_kv, np.uint8), None, gu.dev(k, w), gu.dev(v, w))
-    cache.set_option(sv.SV_OPT_CHUNK_SPLITS, 1)
+    cache.set_option(sv.SV_OPT_CHUNK_SPLITS, 1 | TERMS)
     o = torch.empty(n_q, hq, d, device="cuda:0")
     cache.attn_chunk(0, 0, gu.dev(q, w), o, False)
     if ignored:   # (the same with that key left out)
