@@ -34,6 +34,23 @@ def rms_error(o, ref):
     return float(np.sqrt(np.mean((gu.host(o) - ref) ** 2) / np.mean(ref ** 2)))
 
 
+def one_chunk(q, k, v, causal, splits):
+    """sv_attn_chunk of fp32 queries on fp32 keys and values, [tokens][heads][head_dim], without a rotary mode."""
+    (n_q, hq, d), (n_kv, hkv, _) = q.shape, k.shape
+    cache = sv.Cache(1, hq, hkv, d, sv.SV_DTYPE_F32, sv.SV_ROPE_NONE, 1e4, (0, 0, 0), 1, n_kv + 8, n_q)
+    cache.set_option(sv.SV_OPT_CHUNK_SPLITS, splits)
+    q, k, v = (torch.from_numpy(np.ascontiguousarray(x, np.float32)).to("cuda:0") for x in (q, k, v))
+    cache.append(0, 0, np.zeros(n_kv, np.uint8), None, k, v)
+    o = torch.empty_like(q)
+    cache.attn_chunk(0, 0, q, o, causal)
+    return o
+
+
+def exact_chunk(q, k, v, causal):
+    n_q, n_kv = len(q), len(k)
+    return orc.gqa_attention(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), np.arange(n_kv - n_q, n_kv), causal)
+
+
 def chunk_error(*case):
     return chunk_case(*case)[:2]
 
@@ -190,3 +207,48 @@ def test_fp32_chunk_of_numbers_that_terms_do_not_hold(hq, hkv, d, q_exp, k_exp, 
     ref = orc.gqa_attention(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), np.full(n_q, len(k) - 1), True)
     s = 2.0 ** -v_exp
     assert rms_error(torch.from_numpy(gu.host(o).astype(np.float64) * s), ref * s) <= 3.6 * U
+
+
+def normal(seed, *shape):
+    return np.random.default_rng(seed).standard_normal(shape).astype(np.float32)
+
+
+def one_hot(seed, n, heads, d, dims):
+    """Rows that have one number only, in one of dims."""
+    rng = np.random.default_rng(seed)
+    x = np.zeros((n, heads, d), np.float32)
+    np.put_along_axis(x, rng.choice(dims, (n, heads, 1)), rng.standard_normal((n, heads, 1)).astype(np.float32), 2)
+    return x
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (8, 8, 64)])
+@pytest.mark.parametrize("what", ["queries", "keys", 0, 1, 2, 3])
+def test_fp32_chunk_scores_that_are_one_product(hq, hkv, d, what):
+    """Queries (anywhere, in the i-th quarter of the head dims) or keys of a single number: a score is one product, which an fp32
+    instruction rounds (2^-25.2 of it in the mean) and of which the six products of bf16 terms leave out 2^-27.4.  With nothing
+    else lost on the way the error, which such scores dominate, is no larger than by fp32 instructions."""
+    n, n_q = 1024, 256
+    k, v, q = normal(1, n, hkv, d), normal(2, n, hkv, d), normal(3, n_q, hq, d) * np.float32(16)   # scores of N(0, 16^2)
+    if what == "keys":
+        k = one_hot(4, n, hkv, d, np.arange(d)) * np.float32(np.sqrt(d))
+    else:
+        dims = np.arange(d) if what == "queries" else np.arange(d // 4) + d // 4 * what
+        q = one_hot(5, n_q, hq, d, dims) * np.float32(16 * np.sqrt(d))
+    ref = exact_chunk(q, k, v, False)
+    plain, terms = (rms_error(one_chunk(q, k, v, False, 1 | kind), ref) for kind in (PLAIN, TERMS))
+    print(f"single numbers {what} {hq}/{hkv} x {d}: {plain / U:.2f} and {terms / U:.2f} u", flush=True)
+    assert terms <= plain
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (8, 8, 64)])
+def test_fp32_chunk_of_one_visible_key_is_its_value(hq, hkv, d):
+    """The first query of a causal prefill, and queries of which every weight but one underflows: the value, but for the last place
+    (its weight is 1 and what the score's last addition left: the product and the quotient are rounded, with bf16 terms cut off)."""
+    q, k, v = normal(1, 400, hq, d), normal(2, 400, hkv, d), normal(3, 400, hkv, d)
+    far = -np.abs(k)
+    far[333] *= -100
+    for kind in (PLAIN, TERMS):
+        one = gu.host(one_chunk(q, k, v, True, 1 | kind))[0], np.repeat(v[0], hq // hkv, 0)
+        sole = gu.host(one_chunk(np.abs(q), far, v, False, 3 | kind)), np.repeat(v[333], hq // hkv, 0)[None]
+        for o, x in (one, sole):
+            assert (np.abs(o - x) <= np.spacing(np.abs(x))).all()
