@@ -252,3 +252,29 @@ def test_fp32_chunk_of_one_visible_key_is_its_value(hq, hkv, d):
         sole = gu.host(one_chunk(np.abs(q), far, v, False, 3 | kind)), np.repeat(v[333], hq // hkv, 0)[None]
         for o, x in (one, sole):
             assert (np.abs(o - x) <= np.spacing(np.abs(x))).all()
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (8, 8, 64)])
+@pytest.mark.parametrize("kind", [PLAIN, TERMS])
+@pytest.mark.parametrize("v_exp", [40, 60, 100])
+def test_fp32_chunk_of_weights_that_terms_would_not_hold(hq, hkv, d, kind, v_exp):
+    """Head dims whose only values lie behind weights of 2^-97 to 2^-124 of the largest, and are large enough to matter: the weights keep
+    their 24 bits, as the others do (a bf16 term ends at 2^-133: a weight of 2^-117 would be off by 8e-6 of itself, one of 2^-125 by
+    2e-3).  The scores are one product of few bits, and exact."""
+    n, n_q, far = 330, 140, np.arange(20, 330, 10)
+    rng = np.random.default_rng(d + v_exp)
+    unit = 16 if d == 128 else 8
+    q, k, v = np.zeros((n_q, hq, d), np.float32), normal(2, n, hkv, d), normal(3, n, hkv, d)
+    q[:, :, 7] = unit * (1 + rng.integers(0, 9, (n_q, hq)) / 64)
+    k[:, :, 7] = rng.integers(-8, 9, (n, hkv)) / 8
+    k[12, :, 7] = 2
+    k[far, :, 7] = 2 - np.round(8 * np.linspace(67, 76, len(far)) * np.sqrt(d) / unit)[:, None] / 8   # at most 76.2 x 9 / 8 = 85.8 nats
+    v[:, :, d // 2:] = 0
+    for i, t in enumerate(far):   # every such key has head dims of its own
+        own = np.arange(d // 2 + i, d, len(far))
+        v[t, :, own] = normal(100 + i, len(own), hkv) * np.float32(2.0 ** v_exp)
+    ref = exact_chunk(q, k, v, False)
+    o = gu.host(one_chunk(q, k, v, False, 1 | kind)).astype(np.float64)
+    err = np.sqrt(np.mean((o[..., d // 2:] / ref[..., d // 2:] - 1) ** 2, (0, 1)))   # (a number is one product)
+    print(f"small weights {hq}/{hkv} x {d} 2^{v_exp} terms={kind == TERMS}: {err.max() / U:.2f} u", flush=True)
+    assert err.max() <= 3.6 * U
