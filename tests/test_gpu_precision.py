@@ -278,3 +278,25 @@ def test_fp32_chunk_of_weights_that_terms_would_not_hold(hq, hkv, d, kind, v_exp
     err = np.sqrt(np.mean((o[..., d // 2:] / ref[..., d // 2:] - 1) ** 2, (0, 1)))   # (a number is one product)
     print(f"small weights {hq}/{hkv} x {d} 2^{v_exp} terms={kind == TERMS}: {err.max() / U:.2f} u", flush=True)
     assert err.max() <= 3.6 * U
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (8, 8, 64)])
+@pytest.mark.parametrize("kind", [PLAIN, TERMS])
+@pytest.mark.parametrize("v_exp", [-104, -109, -112, -120, -127, -134, -140])
+@pytest.mark.parametrize("dims", [4, 8, 0])
+def test_fp32_chunk_of_values_that_terms_would_not_hold(hq, hkv, d, kind, v_exp, dims):
+    """Values around 2^-109, below which three bf16 terms lose bits, in the head dims that have a bit (0: in all): as exact as ever, in
+    the first rows of a causal prefill, too, which see few keys.  Results below 2^-126 are multiples of 2^-149."""
+    n = 400
+    q, k, v = normal(1, n, hq, d), normal(2, n, hkv, d), normal(3, n, hkv, d)
+    if v_exp == -109:   # just as large as terms hold
+        v = np.sign(v) * (1 + np.random.default_rng(4).random(v.shape, np.float32))
+    small = (np.arange(d) & dims) != 0 if dims else np.ones(d, bool)
+    v[:, :, small] *= np.float32(2.0 ** v_exp)
+    ref = exact_chunk(q, k, v, True)
+    o = gu.host(one_chunk(q, k, v, True, 1 | kind)).astype(np.float64)
+    e, r = (o - ref)[..., small], ref[..., small]
+    for rows in (8, n):
+        err, size = np.sqrt(np.mean(e[:rows] ** 2)), np.sqrt(np.mean(r[:rows] ** 2))
+        print(f"small values {hq}/{hkv} x {d} 2^{v_exp} bit {dims} terms={kind == TERMS} rows={rows}: {err / size / U:.2f} u", flush=True)
+        assert err <= 3.6 * U * size + 2.0 ** -149
