@@ -344,7 +344,8 @@ def test_decode_lists_longer_than_the_arena_has_rows_for(hq, hkv, d, n_s, layers
 @pytest.mark.parametrize("hq,hkv,d,lens", [
     (8, 2, 128, [1, 15, 16, 17, 64, 65, 500]), (2, 1, 64, [700, 3]), (21, 3, 128, [1500, 129, 128]),
     (7, 1, 64, [40 + 13 * i for i in range(70)]),                      # more rows than one launch takes
-    (8, 8, 128, [7000, 6000])])                                         # 106 MB of K and V: non-temporal loads
+    # 101 MB of K and V and more: non-temporal loads, one to four and more heads per kv head
+    (8, 8, 128, [7000, 6000]), (56, 8, 128, [7000, 6000]), (16, 8, 64, [13000, 11800]), (40, 8, 64, [13000, 11800])])
 def test_fp32_decode_batch_values(hq, hkv, d, lens):
     """Several fp32 rows in a launch: sv_attn_decode, then a fused sv_decode_step with the K and V it stores (rows of one
     tile, of one key range, of many, and their merge)."""
@@ -375,13 +376,14 @@ def test_fp32_decode_batch_values(hq, hkv, d, lens):
     assert gu.max_err(gu.host(od), batch_ref(np.stack(qr), kv2, [n + 1 for n in lens], hq // hkv)) <= gu.TOL["f32"]
 
 
-def test_fp32_decode_of_one_long_stream():
-    """12400 keys of 8 kv heads of 128, 102 MB: the single-stream kernel with non-temporal loads."""
-    cache, w, q, k, v = attn_case("f32", 8, 8, 128, 12400, 1, True, 9800)
+@pytest.mark.parametrize("hq,d,n", [(8, 128, 12400), (56, 128, 12400), (16, 64, 24700), (40, 64, 24700)])
+def test_fp32_decode_of_one_long_stream(hq, d, n):
+    """101 MB of 8 kv heads: the single-stream kernels (one to four heads per kv head, and more) with non-temporal loads."""
+    cache, w, q, k, v = attn_case("f32", hq, 8, d, n, 1, True, 9800)
     qd = gu.dev(q, w)
     od = torch.empty_like(qd)
     cache.attn_decode(0, [0], qd, od)
-    ref = orc.gqa_attention(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), np.array([12399]), True)
+    ref = orc.gqa_attention(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), np.array([n - 1]), True)
     assert gu.max_err(gu.host(od), ref) <= gu.TOL["f32"]
 
 
