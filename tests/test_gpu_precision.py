@@ -173,7 +173,7 @@ def test_fp32_infinite_value_stays_infinite(hq, hkv, d):
     (8, 2, 128, 416, 33, False, 1), (8, 2, 128, 1031, 65, True, 2), (6, 6, 128, 700, 129, True, 1), (28, 4, 128, 1500, 200, True, 3),
     (2, 1, 64, 320, 320, True, 1), (8, 8, 64, 353, 161, False, 1), (14, 2, 64, 2000, 90, True, 4)])
 def test_fp32_chunk_from_bf16_terms_is_as_exact_as_its_sums(hq, hkv, d, n_kv, n_q, causal, splits):
-    """The kernel whose products are made of bf16 terms, on four and more tiles of 32 keys per range: the bound of the fp32
+    """The kernel whose products are made of bf16 terms, on ranges of 10 to 22 tiles of 32 keys: the bound of the fp32
     instructions (what the six products leave out and the matrix cores' rounding are in what is measured below it), and other
     bits than theirs."""
     err, _, o = chunk_case("f32", hq, hkv, d, n_kv, n_q, causal, splits | TERMS)
@@ -243,15 +243,24 @@ def test_fp32_chunk_scores_that_are_one_product(hq, hkv, d, what):
 @pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (8, 8, 64)])
 def test_fp32_chunk_of_one_visible_key_is_its_value(hq, hkv, d):
     """The first query of a causal prefill, and queries of which every weight but one underflows: the value, but for the last place
-    (its weight is 1 and what the score's last addition left: the product and the quotient are rounded, with bf16 terms cut off)."""
-    q, k, v = normal(1, 400, hq, d), normal(2, 400, hkv, d), normal(3, 400, hkv, d)
-    far = -np.abs(k)
-    far[333] *= -100
+    (its weight is 1 and what the score's last addition left: the product is rounded, and the quotient).  By bf16 terms the product is
+    the sum of one exact large product and of small ones that are known to 2^-8 of a last place and off by as much, 2^-27.4 and more, as
+    they leave out: one in 32 may round the other way."""
+    off = {}
     for kind in (PLAIN, TERMS):
-        one = gu.host(one_chunk(q, k, v, True, 1 | kind))[0], np.repeat(v[0], hq // hkv, 0)
-        sole = gu.host(one_chunk(np.abs(q), far, v, False, 3 | kind)), np.repeat(v[333], hq // hkv, 0)[None]
-        for o, x in (one, sole):
-            assert (np.abs(o - x) <= np.spacing(np.abs(x))).all()
+        n_off = 0
+        for seed in range(8):
+            q, k, v = normal(1 + 10 * seed, 160, hq, d), normal(2 + 10 * seed, 160, hkv, d), normal(3 + 10 * seed, 160, hkv, d)
+            far = -np.abs(k)
+            far[133] *= -100
+            one = gu.host(one_chunk(q, k, v, True, 1 | kind))[0], np.repeat(v[0], hq // hkv, 0)
+            sole = gu.host(one_chunk(np.abs(q), far, v, False, 2 | kind)), np.repeat(v[133], hq // hkv, 0)[None]
+            for o, x in (one, sole):
+                assert (np.abs(o - x) <= np.spacing(np.abs(x))).all()
+            n_off += np.mean(one[0] != one[1]) / 8
+        off[kind] = n_off
+    print(f"one visible key {hq}/{hkv} x {d}: {off[PLAIN]:.4f} and {off[TERMS]:.4f} of the numbers are off", flush=True)
+    assert off[TERMS] <= off[PLAIN] + 1 / 32
 
 
 @pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (8, 8, 64)])
