@@ -71,9 +71,9 @@ struct StreamState {
   int64_t still[2] = {0, 0};
 };
 
-// Key ranges of the last chunk-prefill launch and the counts they were chosen for: the layers of a chunk ask in turn.
 enum class F32Chunk : uint8_t { plain, few, terms };   // kernels of fp32 chunk prefill
 
+// Key ranges of the last chunk-prefill launch and the counts they were chosen for: the layers of a chunk ask in turn.
 struct ChunkPlan {
   int n_q = 0, n_kv = 0;
   bool causal = false;
